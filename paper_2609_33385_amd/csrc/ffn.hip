@@ -429,11 +429,24 @@ __global__ __launch_bounds__(kThreads) void k_ffn_mix(FfnLaunch d, FfnLaunch u, 
 //    output row. (Gate/up keeps weights as A: a lane then holds four
 //    consecutive features of a row for its gate and up products.)
 // Every output sums its K range in ascending order in one accumulator (the
-// same products and order either way round). Tiles are ordered feature tile
-// major, so the row tiles of one expert that share weights run next to each
-// other on one XCD (its L2).
+// same products and order either way round), so the cut of an expert's rows
+// into items changes no bit.
+// What bounds it. Below a few hundred rows per expert, what crosses the
+// fabric: with all 256-row items of the launch first and each expert's short
+// item later, the weights of an expert with 375 rows were fetched twice and
+// the gate/up launch of 3001 tokens x 64 experts (hidden 2048) fetched 1.14 GB
+// for 0.55 GB of weights and rows, at 4.3 TB/s. With equal items, one expert
+// after the other and each XCD on its own eighth (k_ffn_dense), gate/up and
+// down of that shape went from 290 + 180 to 231 + 147 us, of 1024 tokens x 128
+// experts (hidden 4096, popular experts) from 325 + 188 to 282 + 153 us, and of
+// 16384 tokens from 3.19 + 2.04 to 2.85 + 1.80 ms (1160 and 915 TFLOP/s), where
+// the clock the part holds under the load bounds it.
+// Measured and not taken: 128-row tiles with two workgroups per CU (within 3%
+// below a thousand rows per expert, 4% slower above); groups of 3 and of 10
+// items (1-5% slower at 16384 tokens); non-temporal weight loads (4.5 against
+// 3.3 ms at 16384 tokens: the row items of an expert no longer share them).
 constexpr int kDenseRing = 4;     // token stages in LDS
-constexpr int kDenseGroup = 4;    // items per tile group
+constexpr int kDenseGroup = 6;    // most items per tile group
 
 // Word 3 of a raw buffer resource (32-bit data format) on this part.
 constexpr int kBufferFlags = 0x00020000;
@@ -495,19 +508,15 @@ __device__ __forceinline__ void wait_lgkm1(u32x4_t& b) {
 // a next quarter follow it (NT - 1 - n reads issued after it).
 template <int NT>
 __device__ __forceinline__ void wait_last(u32x4_t& b, int n) {
-  if constexpr (NT == 8) {
-    switch (n) {
-      case 0: wait_lgkm1<7>(b); break;
-      case 1: wait_lgkm1<6>(b); break;
-      case 2: wait_lgkm1<5>(b); break;
-      case 3: wait_lgkm1<4>(b); break;
-      case 4: wait_lgkm1<3>(b); break;
-      case 5: wait_lgkm1<2>(b); break;
-      case 6: wait_lgkm1<1>(b); break;
-      default: wait_lgkm1<0>(b); break;
-    }
-  } else {
-    wait_lgkm1<0>(b);
+  switch (NT - 1 - n) {
+    case 7: wait_lgkm1<7>(b); break;
+    case 6: wait_lgkm1<6>(b); break;
+    case 5: wait_lgkm1<5>(b); break;
+    case 4: wait_lgkm1<4>(b); break;
+    case 3: wait_lgkm1<3>(b); break;
+    case 2: wait_lgkm1<2>(b); break;
+    case 1: wait_lgkm1<1>(b); break;
+    default: wait_lgkm1<0>(b); break;
   }
 }
 
@@ -726,62 +735,90 @@ __device__ __forceinline__ void dense_tile(const FfnLaunch& a, const WorkItem& i
     }
   } else {
     // lane l holds feature 32 t + l%32 of the wavefront's 64 and, for
-    // register r, token row 8 (r/4) + 4 (l/32) + r%4 of token tile n
+    // register r, token row 8 (r/4) + 4 (l/32) + r%4 of token tile n. Stores
+    // go through a buffer resource of the item's rows, so rows past its end
+    // are dropped without a compare each.
+    const __amdgpu_buffer_rsrc_t ors = __builtin_amdgcn_make_buffer_rsrc(
+        a.oout + static_cast<size_t>(it.row_begin) * H, 0, it.rows * H * 4, kBufferFlags);
+    const int base = 4 * (4 * hi * H + f0 + 64 * wave + col);
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      float* o = a.oout + f0 + 64 * wave + 32 * t + col;
+    for (int n = 0; n < NT; ++n)
 #pragma unroll
-      for (int n = 0; n < NT; ++n)
+      for (int r = 0; r < 16; ++r) {
+        const int off = base + (32 * n + 8 * (r >> 2) + (r & 3)) * (4 * H);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = 32 * n + 8 * (r >> 2) + 4 * hi + (r & 3);
-          if (row < it.rows) o[static_cast<size_t>(it.row_begin + row) * H] = acc[t][n][r];
-        }
-    }
+        for (int t = 0; t < 2; ++t)
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[t][n][r]), ors, off + 128 * t,
+                                                0, 0);
+      }
   }
 }
 
-// Dense launch: one tile per workgroup. Items [0, c0) hold 256 rows each
-// and [c0, c0 + c1) fewer ((c0, c1) = item_counts on the device); full tiles
-// come first in dispatch order and the short ones last, so the hardware's
-// in-order dispatch balances the CUs. Within each class the tiles are spread
-// over the XCDs in contiguous ranges.
+// Dense launch: one tile per workgroup. The tiles are numbered expert by
+// expert; within an expert its items go in groups of at most kDenseGroup,
+// feature tile major inside a group. Workgroup b takes tile j = b / 8 of XCD
+// b % 8, whose contiguous range [dense_start[x], dense_start[x+1]) holds an
+// eighth of the tiles' cost. So the tiles running at once on an XCD are all
+// items of one or two experts against a few weight slices: each weight slice
+// and each token block crosses the fabric once, and is then shared through
+// that XCD's L2. The expert of a tile is found by the wavefront at once (4
+// table entries a lane, a ballot), one load deep.
 template <bool UP>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void k_ffn_dense(FfnLaunch a) {
   __shared__ u32x4_t s_ring[kDenseRing][32][64];
   constexpr int DF = UP ? 128 : 256;
-  const int n_full = a.item_counts[0], n_short = a.item_counts[1];
+  const int lane = threadIdx.x & 63;
   const int nf = (UP ? a.I : a.H) / DF;
-  const int t = blockIdx.x;
-  int v, n, first;
-  if (t < n_full * nf) {
-    v = xcd_order(t, n_full * nf);
-    n = n_full;
-    first = 0;
-  } else {
-    const int u = t - n_full * nf;
-    if (u >= n_short * nf) return;
-    v = xcd_order(u, n_short * nf);
-    n = n_short;
-    first = n_full;
-  }
-  // groups of kDenseGroup items, feature tile major inside a group: the
-  // tiles running at once on an XCD share a few token row blocks and a few
-  // weight slices through its L2
-  const int gsz = kDenseGroup * nf;
-  const int g = v / gsz, rem = v - g * gsz;
-  const int gi = min(kDenseGroup, n - g * kDenseGroup);
-  const int ft = rem / gi;
-  const WorkItem it = a.items[a.item_base + first + g * kDenseGroup + (rem - ft * gi)];
+  const int x = blockIdx.x & 7;
+  const int4* tab = reinterpret_cast<const int4*>(a.dense_tab);
+  int4 ent[kMaxExperts / 64];
+#pragma unroll
+  for (int q = 0; q < kMaxExperts / 64; ++q) ent[q] = tab[lane + 64 * q];
+  const int t = a.dense_start[x] + static_cast<int>(blockIdx.x >> 3);
+  if (t >= a.dense_start[x + 1]) return;
+  int g = -1;   // the last expert whose first tile is at most t
+#pragma unroll
+  for (int q = 0; q < kMaxExperts / 64; ++q)
+    g += __popcll(__ballot(ent[q].x != kDenseNone &&
+                           static_cast<int64_t>(ent[q].x) * nf <= t));
+  if (g < 0) return;
+  int4 mine = ent[0];
+#pragma unroll
+  for (int q = 1; q < kMaxExperts / 64; ++q)
+    if (g >> 6 == q) mine = ent[q];
+  const int first = __builtin_amdgcn_readlane(mine.x, g & 63);
+  const int row0 = __builtin_amdgcn_readlane(mine.y, g & 63);
+  const int rows_exp = __builtin_amdgcn_readlane(mine.z, g & 63);
+  const int hslot = __builtin_amdgcn_readlane(mine.w, g & 63);
+  const int rows = rows_exp & 0xFFFF, expert = (rows_exp >> 16) & (kMaxExperts - 1);
+  const int m = dense_items(rows), per = dense_item_rows(rows);
+  const int ng = (m + kDenseGroup - 1) / kDenseGroup, gs = (m + ng - 1) / ng;
+  int rem = t - first * nf;
+  const int sub = rem / (gs * nf);
+  rem -= sub * gs * nf;
+  const int gi = min(gs, m - sub * gs);
+  if (gi <= 0) return;
+  const int ft = rem / gi, i = sub * gs + rem - ft * gi;
+  WorkItem it;
+  it.expert = expert;
+  it.row_begin = row0 + i * per;
+  it.rows = min(per, rows - i * per);
+  it.pad = hslot;
   const int slot = it.pad >= 0 ? it.pad : a.slot_of[it.expert];
-  if (slot < 0 || slot >= a.n_slots || it.rows <= 0 || it.rows > kDenseRows) return;
+  if (slot < 0 || slot >= a.n_slots || it.rows <= 0 || it.rows > kDenseRows || ft >= nf) return;
   const uint16_t* W = reinterpret_cast<const uint16_t*>(static_cast<const char*>(a.pool) +
                                                         static_cast<int64_t>(slot) * a.slot_bytes);
-  if (it.rows > 128) dense_tile<UP, 8>(a, it, ft * DF, W, s_ring);
-  else if (it.rows > 64) dense_tile<UP, 4>(a, it, ft * DF, W, s_ring);
-  else if (it.rows > 32) dense_tile<UP, 2>(a, it, ft * DF, W, s_ring);
-  else dense_tile<UP, 1>(a, it, ft * DF, W, s_ring);
+  switch ((it.rows + 31) >> 5) {
+    case 1: dense_tile<UP, 1>(a, it, ft * DF, W, s_ring); break;
+    case 2: dense_tile<UP, 2>(a, it, ft * DF, W, s_ring); break;
+    case 3: dense_tile<UP, 3>(a, it, ft * DF, W, s_ring); break;
+    case 4: dense_tile<UP, 4>(a, it, ft * DF, W, s_ring); break;
+    case 5: dense_tile<UP, 5>(a, it, ft * DF, W, s_ring); break;
+    case 6: dense_tile<UP, 6>(a, it, ft * DF, W, s_ring); break;
+    case 7: dense_tile<UP, 7>(a, it, ft * DF, W, s_ring); break;
+    default: dense_tile<UP, 8>(a, it, ft * DF, W, s_ring); break;
+  }
 }
 
 __global__ __launch_bounds__(kThreads) void k_fetch(char* pool, int64_t slot_bytes, int n_slots,
@@ -875,8 +912,10 @@ hipError_t launch_ffn_down(bool bf16, const FfnLaunch& a, hipEvent_t ev0, hipEve
 hipError_t launch_ffn_dense(bool up, const FfnLaunch& a, hipEvent_t ev0, hipEvent_t ev1,
                             hipStream_t s) {
   if (a.H % 256 || a.I % 256 || a.src_bytes <= 0 || a.src_bytes > INT32_MAX) return hipErrorInvalidValue;
-  const int64_t grid = static_cast<int64_t>(a.max_items) * (up ? a.I / 128 : a.H / 256);
-  if (grid <= 0) return hipSuccess;
+  // an XCD's share of the cost holds at most this many tiles of the least cost
+  const int64_t tiles = static_cast<int64_t>(a.max_items) * (up ? a.I / 128 : a.H / 256);
+  if (tiles <= 0) return hipSuccess;
+  const int64_t grid = 8 * ((tiles * kDenseCostMax + 8 * kDenseCostMin - 1) / (8 * kDenseCostMin) + 2);
   if (grid > INT32_MAX) return hipErrorInvalidValue;
   if (up)
     hipExtLaunchKernelGGL(k_ffn_dense<true>, dim3(static_cast<unsigned>(grid)), dim3(kThreads), 0, s,

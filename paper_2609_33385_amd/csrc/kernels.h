@@ -119,6 +119,18 @@ struct WorkItem {
   int32_t pad;   // a hit's cache slot (fixed until the layer's retention), -1 for a miss
 };
 
+// One expert of the dense-tile launches: rows [row_begin, row_begin + rows) of
+// the expert-sorted route order, cut into dense_items(rows) items of equal
+// size (dense_item_rows, the last one shorter). `first` counts the items of
+// the experts before it (kDenseNone: entry unused).
+struct DenseExpert {
+  int32_t first;
+  int32_t row_begin;
+  int32_t rows_exp;   // rows | expert << 16
+  int32_t slot;       // a hit's cache slot, -1 for a miss
+};
+constexpr int32_t kDenseNone = INT32_MAX;
+
 // Host-to-device transfer of the staged misses done by workgroups of a GEMM
 // launch: bytes [off, off + len) of every staged expert's host block into its
 // slot. Workgroups [0, nblk) of the launch copy; the GEMM tiles follow.
@@ -154,6 +166,8 @@ struct FfnLaunch {
   float* oout;            // down: O [T*k][H]
   FetchArgs fetch;
   int64_t src_bytes;      // dense launches: bytes of src (below 2^31)
+  const DenseExpert* dense_tab;   // dense launches: their experts and tile ranges
+  const int32_t* dense_start;     // [9] of this launch
 };
 
 // Every launcher takes optional (ev0, ev1): if non-null they record the
@@ -180,9 +194,10 @@ struct PermuteOut {
   int32_t* inv_perm;
   WorkItem* items;
   int32_t* item_counts;   // [2] hit items, miss items
-  WorkItem* dense_items;  // experts with at least dense_min rows (0: none)
-  int32_t* dense_counts;  // [2] items of kDenseRows rows, shorter items
+  DenseExpert* dense_tab; // [kMaxExperts] experts with at least dense_min rows (0: none)
+  int32_t* dense_start;   // [2][9] first dense tile of each XCD, and the total (gate/up, down)
   int dense_min;
+  int dense_nf[2];        // feature tiles of the dense gate/up and down launches
   RouteStats* ring;       // device ring of routing records
   StagedList* staged;     // pinned, or null
   const float* gates;     // the layer's gates (read when routes are published)
@@ -242,15 +257,25 @@ hipError_t launch_ffn_mix(bool bf16, const FfnLaunch& d, const FfnLaunch& u, hip
 
 // Dense tiles (bf16; H and I multiples of 256; src below 2 GiB) for experts
 // with at least kDenseMinRows routed rows, hits and misses alike, once all
-// their weights are in their slots. Items of kDenseRows rows first
-// (item_counts[0] of them), then one shorter item per expert
-// (item_counts[1]); up: 128 features x 256 rows per workgroup, down: 256 x
-// 256. Those experts have no items in the streaming lists. The threshold is
-// one row above a streaming work item: an expert the streaming kernels would
-// split into two items (each reading all of its weights) runs as one dense
-// item instead.
+// their weights are in their slots; up: 128 features x at most kDenseRows rows
+// per workgroup, down: 256 x kDenseRows. Those experts have no items in the
+// streaming lists. The threshold is one row above a streaming work item: an
+// expert the streaming kernels would split into two items (each reading all
+// of its weights) runs dense instead. An expert's rows are cut into items of
+// equal size (a multiple of 32 rows), so that its tiles take equal time.
 constexpr int kDenseMinRows = kItemRows + 1;
 constexpr int kDenseRows = 256;
+__host__ __device__ inline int dense_items(int rows) { return (rows + kDenseRows - 1) / kDenseRows; }
+__host__ __device__ inline int dense_item_rows(int rows) {
+  const int m = dense_items(rows);
+  return 32 * (((rows + m - 1) / m + 31) / 32);
+}
+// Cost of one tile in the split of a launch's tiles over the XCDs: its row
+// tiles of 32 plus a constant part. Bounded by kDenseCostMax; an expert with
+// kDenseMinRows rows or more costs at least kDenseCostMin per tile.
+constexpr int kDenseCostBase = 8;
+constexpr int kDenseCostMin = kDenseCostBase + (kDenseMinRows + 31) / 32;
+constexpr int kDenseCostMax = kDenseCostBase + kDenseRows / 32;
 hipError_t launch_ffn_dense(bool up, const FfnLaunch& a, hipEvent_t ev0, hipEvent_t ev1,
                             hipStream_t s);
 

@@ -86,7 +86,6 @@ struct Ctx {
   int cap = 0;       // min(C, E)
   int max_items = 0;
   bool dense_ok = false;  // shapes the dense-tile GEMM takes (bf16, H and I multiples of 256)
-  int max_dense = 0;
   const char* host_pool = nullptr;
   int64_t P = 0;
   std::vector<int64_t> host_block_of;
@@ -107,8 +106,8 @@ struct Ctx {
   unsigned long long* d_sacc = nullptr;  // [E] priority numerators of a many-part scoring
   int32_t* d_ssync = nullptr;      // [2] its completion counter and bad-confidence flag
   WorkItem* d_items = nullptr;
-  WorkItem* d_dense_items = nullptr;
-  int32_t* d_dense_counts = nullptr;
+  oled::DenseExpert* d_dense_tab = nullptr;   // [kMaxExperts] experts of the dense launches
+  int32_t* d_dense_start = nullptr;           // [2][9] their first tile per XCD, and the total
   void* d_h = nullptr;
   float* d_O = nullptr;
   uint64_t* d_score = nullptr;     // [L][E]
@@ -397,8 +396,8 @@ void free_ctx(Ctx* c) {
   c->pool.reset();
   if (c->own_copy) (void)hipStreamDestroy(c->own_copy);
   void* dev[] = {c->d_pool, c->d_topk, c->d_gates, c->d_counts, c->d_offsets, c->d_perm,
-                 c->d_inv, c->d_flag, c->d_item_counts, c->d_sync, c->d_items, c->d_dense_items,
-                 c->d_dense_counts, c->d_h, c->d_O,
+                 c->d_inv, c->d_flag, c->d_item_counts, c->d_sync, c->d_items, c->d_dense_tab,
+                 c->d_dense_start, c->d_h, c->d_O,
                  c->d_score, c->d_hdr, c->d_slot_of, c->d_res, c->d_res_before,
                  c->d_last_counts, c->d_free, c->d_host_addr, c->d_cap, c->d_stat,
                  c->d_chunk, c->d_sacc, c->d_ssync, c->d_iters, c->d_last_use,
@@ -702,11 +701,12 @@ oled_status launch_hits(Ctx* c, int layer, hipStream_t s, int64_t h2d) {
 // item counts are on the device.
 oled_status launch_dense(Ctx* c, int layer, hipStream_t s) {
   const int64_t routes = static_cast<int64_t>(c->cur_T) * c->K;
+  // dense_items over the experts with at least kDenseMinRows rows: an item
+  // holds at least that many rows, and an expert at most one short item
   const int max_items = static_cast<int>(
-      routes / oled::kDenseRows + std::min<int64_t>(c->E, routes / oled::kDenseMinRows));
+      std::min<int64_t>(routes / oled::kDenseMinRows, routes / oled::kDenseRows + c->E));
   FfnLaunch a = ffn_args(c, layer, 0, max_items, 0);
-  a.items = c->d_dense_items;
-  a.item_counts = c->d_dense_counts;
+  a.dense_tab = c->d_dense_tab;
   a.src = c->fwd_x;
   a.src_bytes = static_cast<int64_t>(c->cur_T) * c->H * 2;
   for (int part = 3; part <= 4; ++part) {
@@ -715,6 +715,7 @@ oled_status launch_dense(Ctx* c, int layer, hipStream_t s) {
       a.src = c->d_h;
       a.src_bytes = routes * c->I * 2;
     }
+    a.dense_start = c->d_dense_start + (up ? 0 : 9);
     const int kind = up ? OLED_OP_FFN_DENSE_UP : OLED_OP_FFN_DENSE_DOWN;
     OpEvents ev = op_begin(c, kind);
     HIP_TRY(c, oled::launch_ffn_dense(up, a, ev.a, ev.b, s));
@@ -1111,8 +1112,8 @@ oled_status oled_create(const oled_config* cfg, void** ctx_out) {
   c->max_items = static_cast<int>(routes / oled::kItemRows) + c->E + 1;
   c->dense_ok = c->dtype == OLED_BF16 && c->H % 256 == 0 && c->I % 256 == 0 &&
                 c->Tmax >= oled::kDenseMinRows && routes * c->I * 2 <= INT32_MAX &&
-                static_cast<int64_t>(c->Tmax) * c->H * 2 <= INT32_MAX;
-  c->max_dense = c->dense_ok ? static_cast<int>(routes / oled::kDenseRows) + c->E + 1 : 0;
+                static_cast<int64_t>(c->Tmax) * c->H * 2 <= INT32_MAX &&
+                static_cast<int64_t>(oled::kDenseRows) * c->H * 4 <= INT32_MAX;
   c->host_pool = static_cast<const char*>(cfg->host_pool);
   c->P = cfg->host_pool_blocks;
   c->host_block_of.assign(cfg->host_block_of, cfg->host_block_of + nb);
@@ -1134,8 +1135,8 @@ oled_status oled_create(const oled_config* cfg, void** ctx_out) {
       dev_alloc(&c->d_sacc, c->E) || dev_alloc(&c->d_ssync, 2) ||
       dev_alloc(&c->d_logits, static_cast<size_t>(c->Tmax) * c->E) ||
       dev_alloc(&c->d_items, c->max_items) ||
-      (c->dense_ok && (dev_alloc(&c->d_dense_items, c->max_dense) ||
-                       dev_alloc(&c->d_dense_counts, 2))) ||
+      (c->dense_ok && (dev_alloc(&c->d_dense_tab, oled::kMaxExperts) ||
+                       dev_alloc(&c->d_dense_start, 18))) ||
       dev_alloc(reinterpret_cast<char**>(&c->d_h), routes * c->I * c->esz) ||
       dev_alloc(&c->d_O, routes * c->H) ||
       dev_alloc(&c->d_score, static_cast<size_t>(c->L) * c->E))
@@ -1298,8 +1299,10 @@ oled_status route_impl(Ctx* c, int32_t layer, const float* logits_dev, int32_t T
   // experts with many rows go to the dense-tile GEMM; a token picks an expert
   // at most once, so no expert of a block of fewer tokens can have that many
   o.dense_min = c->dense_ok && T >= oled::kDenseMinRows ? oled::kDenseMinRows : 0;
-  o.dense_items = c->d_dense_items;
-  o.dense_counts = c->d_dense_counts;
+  o.dense_tab = c->d_dense_tab;
+  o.dense_start = c->d_dense_start;
+  o.dense_nf[0] = c->I / 128;
+  o.dense_nf[1] = c->H / 256;
   o.ring = c->d_ring;
   o.staged = (c->copy_mode == OLED_COPY_SDMA || c->coop) ? c->h_staged : nullptr;
   o.gates = c->d_gates;

@@ -531,6 +531,11 @@ __device__ __forceinline__ void rank_chunk(const int32_t* idx, int t0, int t1, i
   __syncthreads();
 }
 
+// Cost of an expert's dense tiles per feature tile (see kDenseCostBase).
+__device__ __forceinline__ int dense_cost(int rows) {
+  return dense_items(rows) * (kDenseCostBase + dense_item_rows(rows) / 32);
+}
+
 // Histogram, offsets, work list and stable permutation of the T*k routes in
 // `idx` (global or LDS), by one workgroup, plus the staging of the layer's
 // misses. Pass 1: per-expert counts (LDS atomics). Wave 0 then scans the
@@ -553,8 +558,9 @@ __device__ __forceinline__ void permute_body(const int32_t* idx, int T, int k, i
   __shared__ int32_t s_item_base[kMaxExperts];
   __shared__ int32_t s_run[kMaxExperts];
   __shared__ int32_t s_stat[18];
-  __shared__ int32_t s_dfull[kMaxExperts];   // first full dense item of the expert, or -1
-  __shared__ int32_t s_dshort[kMaxExperts];  // its short dense item, or -1
+  __shared__ int32_t s_dexp[kMaxExperts];    // the expert's entry in the dense table, or -1
+  __shared__ int32_t s_dfirst[kMaxExperts];  // dense items of the experts before it
+  __shared__ int32_t s_dcost[kMaxExperts];   // cost of their tiles (per feature tile)
   __shared__ int32_t s_sexp[kMaxExperts];
   __shared__ int32_t s_sslot[kMaxExperts];
   __shared__ uint32_t s_mask[kMaskRows * kMaskStride];
@@ -602,7 +608,7 @@ __device__ __forceinline__ void permute_body(const int32_t* idx, int T, int k, i
     const int lane = tid;
     int c[4], nh[4], nm[4];
     bool hit[4], miss[4], dn[4];
-    int sc = 0, sh = 0, sm = 0, sx = 0, sdf = 0, sds = 0;
+    int sc = 0, sh = 0, sm = 0, sx = 0, sdi = 0, sdc = 0;
     int n_act = 0, n_hit = 0, n_res = 0, hrows = 0, mrows = 0, n_px = 0, n_rx = 0;
     int n_dense = 0, n_dhit = 0, drows = 0, dhrows = 0;
 #pragma unroll
@@ -616,8 +622,8 @@ __device__ __forceinline__ void permute_body(const int32_t* idx, int T, int k, i
       dn[q] = o.dense_min > 0 && c[q] >= o.dense_min;
       nh[q] = hit[q] && !dn[q] ? ni : 0;
       nm[q] = miss[q] && !dn[q] ? ni : 0;
-      sdf += dn[q] ? c[q] / kDenseRows : 0;
-      sds += dn[q] && c[q] % kDenseRows ? 1 : 0;
+      sdi += dn[q] ? dense_items(c[q]) : 0;
+      sdc += dn[q] ? dense_cost(c[q]) : 0;
       n_dense += dn[q] ? 1 : 0;
       n_dhit += dn[q] && hit[q] ? 1 : 0;
       drows += dn[q] ? c[q] : 0;
@@ -648,13 +654,15 @@ __device__ __forceinline__ void permute_body(const int32_t* idx, int T, int k, i
     const int n_miss = wave_total(ix);
     const int tot_routes = wave_total(ic);
     const int tot_miss_items = wave_total(im);
-    int idf = 0, ids = 0, tot_full = 0, tot_short = 0;
+    int idi = 0, idc = 0, idn = 0, tot_ditems = 0, tot_dcost = 0;
+    const int my_dense = n_dense;
     if (o.dense_min > 0) {
-      idf = wave_incl_scan(sdf);
-      ids = wave_incl_scan(sds);
-      tot_full = wave_total(idf);
-      tot_short = wave_total(ids);
-      n_dense = wave_total(wave_incl_scan(n_dense));
+      idi = wave_incl_scan(sdi);
+      idc = wave_incl_scan(sdc);
+      idn = wave_incl_scan(n_dense);
+      tot_ditems = wave_total(idi);
+      tot_dcost = wave_total(idc);
+      n_dense = wave_total(idn);
       n_dhit = wave_total(wave_incl_scan(n_dhit));
       drows = wave_total(wave_incl_scan(drows));
       dhrows = wave_total(wave_incl_scan(dhrows));
@@ -664,16 +672,17 @@ __device__ __forceinline__ void permute_body(const int32_t* idx, int T, int k, i
     const int free_top = *s_ftop;
     const bool stage = cache && !bad && free_top >= 0 && free_top <= o.cv.n_slots &&
                        n_miss <= free_top;
-    int xc = ic - sc, xh = ih - sh, xm = im - sm, xx = ix - sx, xdf = idf - sdf,
-        xds = tot_full + ids - sds;
+    int xc = ic - sc, xh = ih - sh, xm = im - sm, xx = ix - sx, xdi = idi - sdi, xdc = idc - sdc,
+        xdn = idn - my_dense;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int e = 4 * lane + q;
       if (e < E) {
         s_off[e] = xc;
         s_item_base[e] = (nh[q] > 0) ? xh : tot_hit + xm;
-        s_dfull[e] = dn[q] ? xdf : -1;
-        s_dshort[e] = dn[q] && c[q] % kDenseRows ? xds : -1;
+        s_dexp[e] = dn[q] ? xdn : -1;
+        s_dfirst[e] = xdi;
+        s_dcost[e] = xdc;
         if (stage && miss[q]) {
           const int slot = s_free[xx];
           o.cv.slot_of[static_cast<size_t>(layer) * E + e] = slot;
@@ -687,8 +696,9 @@ __device__ __forceinline__ void permute_body(const int32_t* idx, int T, int k, i
       xh += nh[q];
       xm += nm[q];
       xx += miss[q] ? 1 : 0;
-      xdf += dn[q] ? c[q] / kDenseRows : 0;
-      xds += dn[q] && c[q] % kDenseRows ? 1 : 0;
+      xdi += dn[q] ? dense_items(c[q]) : 0;
+      xdc += dn[q] ? dense_cost(c[q]) : 0;
+      xdn += dn[q] ? 1 : 0;
     }
     // this iteration's transferred misses, for the next one: expert e = 4 lane + q
     // is bit 4 (lane % 8) + q of word lane / 8
@@ -737,8 +747,8 @@ __device__ __forceinline__ void permute_body(const int32_t* idx, int T, int k, i
       s_stat[11] = n_dhit;
       s_stat[12] = drows;
       s_stat[13] = dhrows;
-      s_stat[14] = tot_full;
-      s_stat[15] = tot_short;
+      s_stat[14] = tot_ditems;
+      s_stat[15] = tot_dcost;
     }
     if (cache && lane < kMaxExperts / 32) o.cv.res_before[layer].bits[lane] = s_res[lane];
   }
@@ -753,12 +763,21 @@ __device__ __forceinline__ void permute_body(const int32_t* idx, int T, int k, i
     // a hit's slot cannot change before the layer's retention: the GEMMs take
     // it from the item; a miss's slot is looked up when its GEMM runs
     const int hslot = ((s_res[e >> 5] >> (e & 31)) & 1u) ? s_slot[e] : -1;
-    if (s_dfull[e] >= 0) {  // dense: full items, then the expert's short item
-      const int full = c / kDenseRows;
-      for (int m = 0; m < full; ++m)
-        o.dense_items[s_dfull[e] + m] = WorkItem{e, s_off[e] + m * kDenseRows, kDenseRows, hslot};
-      if (s_dshort[e] >= 0)
-        o.dense_items[s_dshort[e]] = WorkItem{e, s_off[e] + full * kDenseRows, c - full * kDenseRows, hslot};
+    if (s_dexp[e] >= 0) {
+      o.dense_tab[s_dexp[e]] = DenseExpert{s_dfirst[e], s_off[e], c | (e << 16), hslot};
+      // the tiles in expert order cost dense_cost(c) per feature tile: the
+      // XCD boundaries (eighths of the whole) that fall in this expert's
+      // (32 bits: at most 4352 items, kDenseCostMax each, times 8191 feature
+      // tiles; 64-bit divisions here cost the planning 5 us)
+      const uint32_t mine = dense_cost(c), tile = mine / dense_items(c);
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const uint32_t nf = o.dense_nf[p], lo = s_dcost[e] * nf, len = mine * nf;
+        const uint32_t eighth = static_cast<uint32_t>(s_stat[15]) * nf / 8;
+        for (uint32_t x = 0; x < 8; ++x)
+          if (eighth * x - lo < len)   // unsigned: lo <= eighth * x < lo + len
+            o.dense_start[9 * p + x] = s_dfirst[e] * nf + (eighth * x - lo) / tile;
+      }
       continue;
     }
     const int base = s_item_base[e];
@@ -772,6 +791,12 @@ __device__ __forceinline__ void permute_body(const int32_t* idx, int T, int k, i
     }
   }
   if (tid == 0) o.offsets[E] = s_off[E];
+  if (o.dense_min > 0) {   // unused entries, the tile totals, and the starts if there are no tiles
+    for (int e = tid; e < kMaxExperts; e += nthr)
+      if (e >= s_stat[10]) o.dense_tab[e].first = kDenseNone;
+    for (int i = tid; i < 18; i += nthr)
+      if (i % 9 == 8 || s_stat[14] == 0) o.dense_start[i] = s_stat[14] * o.dense_nf[i / 9];
+  }
 
   if (chunk_base) {   // per-chunk bases for the ranking launch: exclusive scan over chunks
     if (my_g >= 0) {
@@ -812,7 +837,7 @@ __device__ __forceinline__ void permute_body(const int32_t* idx, int T, int k, i
     rs.n_dense_hits = dense ? s_stat[11] : 0;
     rs.dense_rows = dense ? s_stat[12] : 0;
     rs.dense_hit_rows = dense ? s_stat[13] : 0;
-    rs.n_dense_items = dense ? s_stat[14] + s_stat[15] : 0;
+    rs.n_dense_items = dense ? s_stat[14] : 0;
     rs.prev_xfer = s_stat[16];
     rs.reused_xfer = s_stat[17];
     rs.ideal_hits = min(o.cv.cap[layer], s_stat[0]);
@@ -820,10 +845,6 @@ __device__ __forceinline__ void permute_body(const int32_t* idx, int T, int k, i
     if (tid == 0) {
       o.item_counts[0] = s_stat[8];
       o.item_counts[1] = s_stat[9];
-      if (dense) {
-        o.dense_counts[0] = s_stat[14];
-        o.dense_counts[1] = s_stat[15];
-      }
       o.ring[o.seq % kStatsRing] = rs;
     }
     if (o.staged) {
