@@ -652,6 +652,20 @@ oled_status check_slots(Ctx* c) {
 }
 
 
+// Streaming work items of at most n_exp experts of the layer in flight: one
+// each where no expert has more rows than an item (blocks of at most
+// kItemRows tokens, and blocks whose larger experts run as dense tiles). It
+// only sizes the grid (workgroups beyond the live tiles exit, and loop over
+// tiles beyond the grid): an idle workgroup costs about half a nanosecond, so
+// that a bound of one more item per 64 routes cost 3001 tokens x 64 experts
+// (no streaming item at all) 4 us.
+int max_stream_items(const Ctx* c, int n_exp) {
+  if (n_exp <= 0) return 0;
+  const int64_t routes = static_cast<int64_t>(c->cur_T) * c->K;
+  const bool single = c->cur_dense || c->cur_T <= oled::kItemRows;
+  return static_cast<int>(std::min<int64_t>(n_exp, routes) + (single ? 0 : routes / oled::kItemRows));
+}
+
 // The hits' GEMMs: the active residents, at most min(C, E) experts; their
 // item count stays on the device. With the shader transfer the first
 // workgroups of the gate/up launch copy the staged misses' gate/up weights
@@ -660,9 +674,7 @@ oled_status check_slots(Ctx* c) {
 // a launch with the misses' gate/up); with the copy engine it follows at once.
 oled_status launch_hits(Ctx* c, int layer, hipStream_t s, int64_t h2d) {
   const void* x_dev = c->fwd_x;
-  const int64_t routes = static_cast<int64_t>(c->cur_T) * c->K;
-  const int max_hit_items =
-      c->cap > 0 ? static_cast<int>(std::min<int64_t>(c->cap, routes) + routes / oled::kItemRows) : 0;
+  const int max_hit_items = max_stream_items(c, c->cap);
   const bool shader = c->copy_mode == OLED_COPY_SHADER;
   const bool bf16 = c->dtype == OLED_BF16;
   FfnLaunch a = ffn_args(c, layer, 0, max_hit_items, 0);
@@ -931,12 +943,8 @@ void coop_dispatch(int E, const uint8_t* miss, const int32_t* n_tok, const uint6
 // GEMMs, then the dense experts. h2d: bytes of the transferred misses.
 oled_status launch_coop_rest(Ctx* c, int layer, hipStream_t s, int64_t h2d) {
   const bool bf16 = c->dtype == OLED_BF16;
-  const int64_t routes = static_cast<int64_t>(c->cur_T) * c->K;
-  const int max_hit_items =
-      c->cap > 0 ? static_cast<int>(std::min<int64_t>(c->cap, routes) + routes / oled::kItemRows)
-                 : 0;
-  const int max_miss_items =
-      static_cast<int>(std::min<int64_t>(c->E, routes) + routes / oled::kItemRows);
+  const int max_hit_items = max_stream_items(c, c->cap);
+  const int max_miss_items = max_stream_items(c, c->E);
   FfnLaunch d = ffn_args(c, layer, 0, max_hit_items, 0);
   d.src = c->d_h;
   if (h2d > 0) {
@@ -978,12 +986,8 @@ oled_status launch_coop_rest(Ctx* c, int layer, hipStream_t s, int64_t h2d) {
 // misses, or -1 to take them from the routing record.
 oled_status launch_shader_rest(Ctx* c, int layer, hipStream_t s, int64_t h2d) {
   const bool bf16 = c->dtype == OLED_BF16;
-  const int64_t routes = static_cast<int64_t>(c->cur_T) * c->K;
-  const int max_hit_items =
-      c->cap > 0 ? static_cast<int>(std::min<int64_t>(c->cap, routes) + routes / oled::kItemRows)
-                 : 0;
-  const int max_miss_items =
-      static_cast<int>(std::min<int64_t>(c->E, routes) + routes / oled::kItemRows);
+  const int max_hit_items = max_stream_items(c, c->cap);
+  const int max_miss_items = max_stream_items(c, c->E);
   FfnLaunch d = ffn_args(c, layer, 0, max_hit_items, 0);
   d.src = c->d_h;
   d.fetch.nblk = kFetchBlocks;
