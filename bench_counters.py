@@ -24,7 +24,8 @@ them in order:
   k_ffn_mix<...>          cached experts' down GEMM + the misses' down copy
                           + the misses' gate/up GEMM          <- ffn_down, 1st of each layer
   k_ffn<..., false, ...>  the misses' down GEMM               <- ffn_down, 2nd of each layer
-  k_ffn_dense<true/false> dense tiles                        <- ffn_dense_up / _down
+  k_ffn_dense<true/false> dense tiles of launches of their own <- ffn_dense_up / _down
+                          (small ones ride in the mix and down launches)
 """
 from __future__ import annotations
 

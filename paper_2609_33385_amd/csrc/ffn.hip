@@ -368,39 +368,6 @@ __device__ __forceinline__ void gemm_tiles(const FfnLaunch& a, int t0, int strid
   }
 }
 
-template <class TR, bool UP, int KS>
-__global__ __launch_bounds__(kThreads) void k_ffn(FfnLaunch a) {
-  __shared__ floatx4_t s_red[KS > 1 ? kWaves : 1][(UP ? 2 : 1) * kMaxNT][64];
-  const int nfetch = a.fetch.nblk;
-  const int b = blockIdx.x;
-  if (b < nfetch) {
-    fetch_blocks(a.fetch, static_cast<char*>(const_cast<void*>(a.pool)), a.slot_bytes, a.n_slots, b);
-    return;
-  }
-  gemm_tiles<TR, UP, KS>(a, b - nfetch, static_cast<int>(gridDim.x) - nfetch, s_red);
-}
-
-// One launch for three independent parts: the transfer of the misses' down
-// weights (workgroups [0, nfetch)), the hit experts' down GEMM (the next gd
-// workgroups) and the misses' gate/up GEMM, whose weights the previous launch
-// transferred (the rest).
-template <class TR, int KSD, int KSU>
-__global__ __launch_bounds__(kThreads) void k_ffn_mix(FfnLaunch d, FfnLaunch u, int gd) {
-  __shared__ floatx4_t s_buf[kWaves][2 * kMaxNT][64];
-  const int nfetch = d.fetch.nblk;
-  const int b = blockIdx.x;
-  if (b < nfetch) {
-    fetch_blocks(d.fetch, static_cast<char*>(const_cast<void*>(d.pool)), d.slot_bytes, d.n_slots, b);
-    return;
-  }
-  if (b < nfetch + gd) {
-    gemm_tiles<TR, false, KSD>(d, b - nfetch, gd,
-                               reinterpret_cast<floatx4_t (*)[kMaxNT][64]>(&s_buf[0][0][0]));
-    return;
-  }
-  gemm_tiles<TR, true, KSU>(u, b - nfetch - gd, static_cast<int>(gridDim.x) - nfetch - gd, s_buf);
-}
-
 // ---------------------------------------------------------------------------
 // Dense tiles for experts with many routed rows (bf16). A workgroup computes
 // up to 256 rows of one expert against 256 weight rows: gate/up 128 features
@@ -537,9 +504,9 @@ using ic_t = std::integral_constant<int, V>;
 // B(s+1) may leave outstanding what was issued after DMA(s+1): all of stage
 // s-1 and q0..q2 of stage s, 14 + NT in steady state (10 two stages from the
 // end, where no DMA and only the last weight quarter remain).
-template <bool UP, int NT>
+template <bool UP, int NT, int RR>
 __device__ __forceinline__ void dense_tile(const FfnLaunch& a, const WorkItem& it, int f0,
-                                           const uint16_t* W, u32x4_t (*ring)[32][64]) {
+                                           const uint16_t* W, u32x4_t (*ring)[RR / 8][64]) {
   constexpr int FRAG = 512;               // packed fragment: 16 rows x 32 of K
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: scalar LDS bases
@@ -621,7 +588,7 @@ __device__ __forceinline__ void dense_tile(const FfnLaunch& a, const WorkItem& i
   }
   const uint32_t ring_base = lds_addr(&ring[0][0][0]);
   auto read1 = [&](int s, int h, int n) {
-    const uint32_t sbase = ring_base + static_cast<uint32_t>(s % kDenseRing) * (32 * 64 * 16);
+    const uint32_t sbase = ring_base + static_cast<uint32_t>(s % kDenseRing) * (RR / 8 * 64 * 16);
     const int c = 2 * h + (lane >> 5);
     return lds_read16(sbase + brow_off[n] + 16 * (c ^ bsw[n]));
   };
@@ -754,28 +721,24 @@ __device__ __forceinline__ void dense_tile(const FfnLaunch& a, const WorkItem& i
   }
 }
 
-// Dense launch: one tile per workgroup. The tiles are numbered expert by
-// expert; within an expert its items go in groups of at most kDenseGroup,
-// feature tile major inside a group. Workgroup b takes tile j = b / 8 of XCD
-// b % 8, whose contiguous range [dense_start[x], dense_start[x+1]) holds an
+// Dense tile b of a launch: the tiles are numbered expert by expert; within an expert its items go in groups of at most kDenseGroup,
+// feature tile major inside a group. b (on XCD b % 8) is tile b / 8 of that XCD, whose contiguous range [dense_start[x], dense_start[x+1]) holds an
 // eighth of the tiles' cost. So the tiles running at once on an XCD are all
 // items of one or two experts against a few weight slices: each weight slice
 // and each token block crosses the fabric once, and is then shared through
 // that XCD's L2. The expert of a tile is found by the wavefront at once (4
 // table entries a lane, a ballot), one load deep.
-template <bool UP>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void k_ffn_dense(FfnLaunch a) {
-  __shared__ u32x4_t s_ring[kDenseRing][32][64];
+template <bool UP, int RR>
+__device__ __forceinline__ void dense_block(const FfnLaunch& a, int b, u32x4_t (*ring)[RR / 8][64]) {
   constexpr int DF = UP ? 128 : 256;
   const int lane = threadIdx.x & 63;
   const int nf = (UP ? a.I : a.H) / DF;
-  const int x = blockIdx.x & 7;
+  const int x = b & 7;
   const int4* tab = reinterpret_cast<const int4*>(a.dense_tab);
   int4 ent[kMaxExperts / 64];
 #pragma unroll
   for (int q = 0; q < kMaxExperts / 64; ++q) ent[q] = tab[lane + 64 * q];
-  const int t = a.dense_start[x] + static_cast<int>(blockIdx.x >> 3);
+  const int t = a.dense_start[x] + (b >> 3);
   if (t >= a.dense_start[x + 1]) return;
   int g = -1;   // the last expert whose first tile is at most t
 #pragma unroll
@@ -792,7 +755,7 @@ void k_ffn_dense(FfnLaunch a) {
   const int rows_exp = __builtin_amdgcn_readlane(mine.z, g & 63);
   const int hslot = __builtin_amdgcn_readlane(mine.w, g & 63);
   const int rows = rows_exp & 0xFFFF, expert = (rows_exp >> 16) & (kMaxExperts - 1);
-  const int m = dense_items(rows), per = dense_item_rows(rows);
+  const int m = dense_items(rows, RR), per = dense_item_rows(rows, RR);
   const int ng = (m + kDenseGroup - 1) / kDenseGroup, gs = (m + ng - 1) / ng;
   int rem = t - first * nf;
   const int sub = rem / (gs * nf);
@@ -806,19 +769,96 @@ void k_ffn_dense(FfnLaunch a) {
   it.rows = min(per, rows - i * per);
   it.pad = hslot;
   const int slot = it.pad >= 0 ? it.pad : a.slot_of[it.expert];
-  if (slot < 0 || slot >= a.n_slots || it.rows <= 0 || it.rows > kDenseRows || ft >= nf) return;
+  if (slot < 0 || slot >= a.n_slots || it.rows <= 0 || it.rows > RR || ft >= nf) return;
   const uint16_t* W = reinterpret_cast<const uint16_t*>(static_cast<const char*>(a.pool) +
                                                         static_cast<int64_t>(slot) * a.slot_bytes);
-  switch ((it.rows + 31) >> 5) {
-    case 1: dense_tile<UP, 1>(a, it, ft * DF, W, s_ring); break;
-    case 2: dense_tile<UP, 2>(a, it, ft * DF, W, s_ring); break;
-    case 3: dense_tile<UP, 3>(a, it, ft * DF, W, s_ring); break;
-    case 4: dense_tile<UP, 4>(a, it, ft * DF, W, s_ring); break;
-    case 5: dense_tile<UP, 5>(a, it, ft * DF, W, s_ring); break;
-    case 6: dense_tile<UP, 6>(a, it, ft * DF, W, s_ring); break;
-    case 7: dense_tile<UP, 7>(a, it, ft * DF, W, s_ring); break;
-    default: dense_tile<UP, 8>(a, it, ft * DF, W, s_ring); break;
+  const int nt = (it.rows + 31) >> 5;
+  if constexpr (RR > 128) {
+    switch (nt) {
+      case 5: dense_tile<UP, 5, RR>(a, it, ft * DF, W, ring); return;
+      case 6: dense_tile<UP, 6, RR>(a, it, ft * DF, W, ring); return;
+      case 7: dense_tile<UP, 7, RR>(a, it, ft * DF, W, ring); return;
+      case 8: dense_tile<UP, 8, RR>(a, it, ft * DF, W, ring); return;
+    }
   }
+  switch (nt) {
+    case 1: dense_tile<UP, 1, RR>(a, it, ft * DF, W, ring); return;
+    case 2: dense_tile<UP, 2, RR>(a, it, ft * DF, W, ring); return;
+    case 3: dense_tile<UP, 3, RR>(a, it, ft * DF, W, ring); return;
+    case 4: dense_tile<UP, 4, RR>(a, it, ft * DF, W, ring); return;
+  }
+}
+
+// A launch of large dense tiles alone.
+template <bool UP>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void k_ffn_dense(FfnLaunch a) {
+  __shared__ u32x4_t s_ring[kDenseRing][kDenseRowsLarge / 8][64];
+  dense_block<UP, kDenseRowsLarge>(a, blockIdx.x, s_ring);
+}
+
+// LDS of a launch in which dense tiles may ride: their ring, or the partial
+// tiles of the streaming part.
+using SmallRing = u32x4_t[kDenseRowsSmall / 8][64];
+template <bool DN, int SLOTS>
+struct TileLds {
+  static constexpr int kRing = kDenseRing * (kDenseRowsSmall / 8) * 64;
+  floatx4_t buf[(DN && kRing > SLOTS * 64) ? kRing : SLOTS * 64];
+};
+
+// DN: workgroups [nfetch, nfetch + ge) take dense tiles.
+template <class TR, bool UP, int KS, bool DN>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DN ? 2 : 1)))
+void k_ffn(FfnLaunch a, int ge) {
+  constexpr int kTiles = (UP ? 2 : 1) * kMaxNT;
+  __shared__ TileLds<DN, (KS > 1 ? kWaves : 1) * kTiles> s_lds;
+  const int nfetch = a.fetch.nblk;
+  const int b = blockIdx.x;
+  if (b < nfetch) {
+    fetch_blocks(a.fetch, static_cast<char*>(const_cast<void*>(a.pool)), a.slot_bytes, a.n_slots, b);
+    return;
+  }
+  if constexpr (DN) {
+    if (b < nfetch + ge) {
+      dense_block<UP, kDenseRowsSmall>(a, b - nfetch, reinterpret_cast<SmallRing*>(s_lds.buf));
+      return;
+    }
+  }
+  gemm_tiles<TR, UP, KS>(a, b - nfetch - ge, static_cast<int>(gridDim.x) - nfetch - ge,
+                         reinterpret_cast<floatx4_t (*)[kTiles][64]>(s_lds.buf));
+}
+
+// One launch for the independent parts between the two waits of a layer: the
+// transfer of the misses' down weights (workgroups [0, nfetch)), the dense
+// tiles of gate/up (DN: the next ge; every gate/up weight is in its slot), the
+// hit experts' down GEMM (the next gd) and the misses' gate/up GEMM, whose
+// weights the previous launch transferred (the rest). The dense tiles, the
+// longest, start first, so that the short streaming tiles fill the CUs as
+// they finish. (As launches of their own the dense parts cost every layer of
+// more than 64 tokens 2 x 4.7 us, also without a dense expert, and a tail each.)
+template <class TR, int KSD, int KSU, bool DN>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DN ? 2 : 1)))
+void k_ffn_mix(FfnLaunch d, FfnLaunch u, int gd, int ge) {
+  __shared__ TileLds<DN, kWaves * 2 * kMaxNT> s_lds;
+  const int nfetch = d.fetch.nblk;
+  const int b = blockIdx.x;
+  if (b < nfetch) {
+    fetch_blocks(d.fetch, static_cast<char*>(const_cast<void*>(d.pool)), d.slot_bytes, d.n_slots, b);
+    return;
+  }
+  if constexpr (DN) {
+    if (b < nfetch + ge) {
+      dense_block<true, kDenseRowsSmall>(u, b - nfetch, reinterpret_cast<SmallRing*>(s_lds.buf));
+      return;
+    }
+  }
+  if (b < nfetch + ge + gd) {
+    gemm_tiles<TR, false, KSD>(d, b - nfetch - ge, gd,
+                               reinterpret_cast<floatx4_t (*)[kMaxNT][64]>(s_lds.buf));
+    return;
+  }
+  gemm_tiles<TR, true, KSU>(u, b - nfetch - ge - gd, static_cast<int>(gridDim.x) - nfetch - ge - gd,
+                            reinterpret_cast<floatx4_t (*)[2 * kMaxNT][64]>(s_lds.buf));
 }
 
 __global__ __launch_bounds__(kThreads) void k_fetch(char* pool, int64_t slot_bytes, int n_slots,
@@ -833,20 +873,7 @@ __global__ __launch_bounds__(kThreads) void k_fetch(char* pool, int64_t slot_byt
 inline int k_split_up(int K) { return K >= 1024 ? 4 : (K >= 512 ? 2 : 1); }
 inline int k_split_down(int K) { return K >= 4096 ? 4 : (K >= 2048 ? 2 : 1); }
 
-int part_grid(const FfnLaunch& a, int nf);
-
-template <class TR, bool UP, int KS>
-hipError_t launch_ffn_ks(const FfnLaunch& a, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s) {
-  if (a.fetch.nblk % 8) return hipErrorInvalidValue;
-  const int64_t grid = static_cast<int64_t>(a.fetch.nblk) +
-                       part_grid(a, (UP ? a.I : a.H) / (kFeat * kFG * (kWaves / KS)));
-  if (grid <= 0) return hipSuccess;
-  hipExtLaunchKernelGGL(k_ffn<TR, UP, KS>, dim3(static_cast<unsigned>(grid)), dim3(kThreads), 0, s,
-                        ev0, ev1, 0, a);
-  return hipGetLastError();
-}
-
-// Workgroups of one GEMM part: max_items * tiles per item, capped at
+// Workgroups of one streaming part: max_items * tiles per item, capped at
 // max_grid, rounded up to a multiple of 8.
 int part_grid(const FfnLaunch& a, int nf) {
   int64_t tiles = static_cast<int64_t>(a.max_items) * nf;
@@ -854,26 +881,60 @@ int part_grid(const FfnLaunch& a, int nf) {
   return static_cast<int>((tiles + 7) & ~static_cast<int64_t>(7));
 }
 
-template <class TR, int KSD, int KSU>
+// Workgroups of one dense part (a multiple of 8): an XCD's share of the cost
+// holds at most this many tiles of the least cost.
+int64_t dense_grid(const FfnLaunch& a, bool up, int R) {
+  const int64_t tiles = static_cast<int64_t>(a.max_dense) * (up ? a.I / 128 : a.H / 256);
+  if (tiles <= 0) return 0;
+  return 8 * ((tiles * dense_cost_max(R) + 8 * kDenseCostMin - 1) / (8 * kDenseCostMin) + 2);
+}
+
+bool dense_shape_ok(const FfnLaunch& a) {
+  return a.H % 256 == 0 && a.I % 256 == 0 && a.src_bytes > 0 && a.src_bytes <= INT32_MAX;
+}
+
+template <class TR, bool UP, int KS, bool DN>
+hipError_t launch_ffn_ks(const FfnLaunch& a, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s) {
+  if (a.fetch.nblk % 8) return hipErrorInvalidValue;
+  const int64_t ge = DN ? dense_grid(a, UP, kDenseRowsSmall) : 0;
+  const int64_t grid = static_cast<int64_t>(a.fetch.nblk) + ge +
+                       part_grid(a, (UP ? a.I : a.H) / (kFeat * kFG * (kWaves / KS)));
+  if (grid <= 0) return hipSuccess;
+  if (grid > INT32_MAX) return hipErrorInvalidValue;
+  hipExtLaunchKernelGGL(k_ffn<TR, UP, KS, DN>, dim3(static_cast<unsigned>(grid)), dim3(kThreads), 0,
+                        s, ev0, ev1, 0, a, static_cast<int>(ge));
+  return hipGetLastError();
+}
+
+template <class TR, int KSD, int KSU, bool DN>
 hipError_t launch_mix_ks(const FfnLaunch& d, const FfnLaunch& u, hipEvent_t ev0, hipEvent_t ev1,
                          hipStream_t s) {
   if (d.fetch.nblk % 8) return hipErrorInvalidValue;
+  const int64_t ge = DN ? dense_grid(u, true, kDenseRowsSmall) : 0;
   const int gd = part_grid(d, d.H / (kFeat * kFG * (kWaves / KSD)));
   const int gu = part_grid(u, u.I / (kFeat * kFG * (kWaves / KSU)));
-  const int64_t grid = static_cast<int64_t>(d.fetch.nblk) + gd + gu;
+  const int64_t grid = static_cast<int64_t>(d.fetch.nblk) + ge + gd + gu;
   if (grid <= 0) return hipSuccess;
-  hipExtLaunchKernelGGL(k_ffn_mix<TR, KSD, KSU>, dim3(static_cast<unsigned>(grid)), dim3(kThreads),
-                        0, s, ev0, ev1, 0, d, u, gd);
+  if (grid > INT32_MAX) return hipErrorInvalidValue;
+  hipExtLaunchKernelGGL(k_ffn_mix<TR, KSD, KSU, DN>, dim3(static_cast<unsigned>(grid)),
+                        dim3(kThreads), 0, s, ev0, ev1, 0, d, u, gd, static_cast<int>(ge));
   return hipGetLastError();
 }
 
 template <class TR, int KSD>
 hipError_t launch_mix_d(const FfnLaunch& d, const FfnLaunch& u, hipEvent_t ev0, hipEvent_t ev1,
                         hipStream_t s) {
+  if constexpr (sizeof(typename TR::T) == 2) {
+    static_assert(kDenseRideHidden >= 1024, "riding dense tiles take gate/up K splits of 4");
+    if (u.max_dense > 0) {
+      if (u.H < kDenseRideHidden || !dense_shape_ok(u)) return hipErrorInvalidValue;
+      return launch_mix_ks<TR, KSD, 4, true>(d, u, ev0, ev1, s);
+    }
+  }
   switch (k_split_up(u.H)) {
-    case 4: return launch_mix_ks<TR, KSD, 4>(d, u, ev0, ev1, s);
-    case 2: return launch_mix_ks<TR, KSD, 2>(d, u, ev0, ev1, s);
-    default: return launch_mix_ks<TR, KSD, 1>(d, u, ev0, ev1, s);
+    case 4: return launch_mix_ks<TR, KSD, 4, false>(d, u, ev0, ev1, s);
+    case 2: return launch_mix_ks<TR, KSD, 2, false>(d, u, ev0, ev1, s);
+    default: return launch_mix_ks<TR, KSD, 1, false>(d, u, ev0, ev1, s);
   }
 }
 
@@ -887,12 +948,23 @@ hipError_t launch_mix_t(const FfnLaunch& d, const FfnLaunch& u, hipEvent_t ev0, 
   }
 }
 
+template <class TR, bool UP, int KS>
+hipError_t launch_ffn_d(const FfnLaunch& a, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s) {
+  if constexpr (!UP && sizeof(typename TR::T) == 2) {
+    if (a.max_dense > 0) {
+      if (!dense_shape_ok(a)) return hipErrorInvalidValue;
+      return launch_ffn_ks<TR, UP, KS, true>(a, ev0, ev1, s);
+    }
+  }
+  return launch_ffn_ks<TR, UP, KS, false>(a, ev0, ev1, s);
+}
+
 template <class TR, bool UP>
 hipError_t launch_ffn_t(const FfnLaunch& a, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s) {
   switch (UP ? k_split_up(a.H) : k_split_down(a.I)) {
-    case 4: return launch_ffn_ks<TR, UP, 4>(a, ev0, ev1, s);
-    case 2: return launch_ffn_ks<TR, UP, 2>(a, ev0, ev1, s);
-    default: return launch_ffn_ks<TR, UP, 1>(a, ev0, ev1, s);
+    case 4: return launch_ffn_d<TR, UP, 4>(a, ev0, ev1, s);
+    case 2: return launch_ffn_d<TR, UP, 2>(a, ev0, ev1, s);
+    default: return launch_ffn_d<TR, UP, 1>(a, ev0, ev1, s);
   }
 }
 
@@ -911,11 +983,9 @@ hipError_t launch_ffn_down(bool bf16, const FfnLaunch& a, hipEvent_t ev0, hipEve
 
 hipError_t launch_ffn_dense(bool up, const FfnLaunch& a, hipEvent_t ev0, hipEvent_t ev1,
                             hipStream_t s) {
-  if (a.H % 256 || a.I % 256 || a.src_bytes <= 0 || a.src_bytes > INT32_MAX) return hipErrorInvalidValue;
-  // an XCD's share of the cost holds at most this many tiles of the least cost
-  const int64_t tiles = static_cast<int64_t>(a.max_items) * (up ? a.I / 128 : a.H / 256);
-  if (tiles <= 0) return hipSuccess;
-  const int64_t grid = 8 * ((tiles * kDenseCostMax + 8 * kDenseCostMin - 1) / (8 * kDenseCostMin) + 2);
+  if (!dense_shape_ok(a)) return hipErrorInvalidValue;
+  const int64_t grid = dense_grid(a, up, kDenseRowsLarge);
+  if (grid <= 0) return hipSuccess;
   if (grid > INT32_MAX) return hipErrorInvalidValue;
   if (up)
     hipExtLaunchKernelGGL(k_ffn_dense<true>, dim3(static_cast<unsigned>(grid)), dim3(kThreads), 0, s,

@@ -120,8 +120,8 @@ struct WorkItem {
 };
 
 // One expert of the dense-tile launches: rows [row_begin, row_begin + rows) of
-// the expert-sorted route order, cut into dense_items(rows) items of equal
-// size (dense_item_rows, the last one shorter). `first` counts the items of
+// the expert-sorted route order, cut into dense_items() items of equal size
+// (dense_item_rows(), the last one shorter). `first` counts the items of
 // the experts before it (kDenseNone: entry unused).
 struct DenseExpert {
   int32_t first;
@@ -166,8 +166,9 @@ struct FfnLaunch {
   float* oout;            // down: O [T*k][H]
   FetchArgs fetch;
   int64_t src_bytes;      // dense launches: bytes of src (below 2^31)
-  const DenseExpert* dense_tab;   // dense launches: their experts and tile ranges
+  const DenseExpert* dense_tab;   // dense tiles: their experts and tile ranges
   const int32_t* dense_start;     // [9] of this launch
+  int max_dense;                  // bound on their items (0: none ride in this launch)
 };
 
 // Every launcher takes optional (ev0, ev1): if non-null they record the
@@ -197,6 +198,7 @@ struct PermuteOut {
   DenseExpert* dense_tab; // [kMaxExperts] experts with at least dense_min rows (0: none)
   int32_t* dense_start;   // [2][9] first dense tile of each XCD, and the total (gate/up, down)
   int dense_min;
+  int dense_shift;        // log2 of the most rows of a dense item (kDenseRowsLarge or Small)
   int dense_nf[2];        // feature tiles of the dense gate/up and down launches
   RouteStats* ring;       // device ring of routing records
   StagedList* staged;     // pinned, or null
@@ -246,36 +248,53 @@ hipError_t launch_route_fused(const float* logits, int T, int k, int32_t* topk_i
 hipError_t launch_ffn_up(bool bf16, const FfnLaunch& a, hipEvent_t ev0, hipEvent_t ev1,
                          hipStream_t s);
 
-// K4b: grouped down GEMM (O = W2 h, fp32).
+// K4b: grouped down GEMM (O = W2 h, fp32), and the dense tiles of down
+// (a.max_dense > 0).
 hipError_t launch_ffn_down(bool bf16, const FfnLaunch& a, hipEvent_t ev0, hipEvent_t ev1,
                            hipStream_t s);
 
-// The hit experts' down GEMM with the transfer of the misses' down weights
+// The hit experts' down GEMM (and the dense tiles of gate/up, u.max_dense > 0)
+// with the transfer of the misses' down weights
 // (d.fetch), and the misses' gate/up GEMM (u), in one launch.
 hipError_t launch_ffn_mix(bool bf16, const FfnLaunch& d, const FfnLaunch& u, hipEvent_t ev0,
                           hipEvent_t ev1, hipStream_t s);
 
 // Dense tiles (bf16; H and I multiples of 256; src below 2 GiB) for experts
 // with at least kDenseMinRows routed rows, hits and misses alike, once all
-// their weights are in their slots; up: 128 features x at most kDenseRows rows
-// per workgroup, down: 256 x kDenseRows. Those experts have no items in the
-// streaming lists. The threshold is one row above a streaming work item: an
-// expert the streaming kernels would split into two items (each reading all
-// of its weights) runs dense instead. An expert's rows are cut into items of
-// equal size (a multiple of 32 rows), so that its tiles take equal time.
+// their weights are in their slots; up: 128 features x at most R rows per
+// workgroup, down: 256 x R. Those experts have no items in the streaming
+// lists. The threshold is one row above a streaming work item: an expert the
+// streaming kernels would split into two items (each reading all of its
+// weights) runs dense instead. An expert's rows are cut into items of equal
+// size (a multiple of 32 rows), so that its tiles take equal time.
+//
+// R = kDenseRowsLarge: launches of their own (launch_ffn_dense), one workgroup
+// per CU. R = kDenseRowsSmall: tiles of half the registers and LDS, two
+// workgroups per CU, which ride in the launches of the streaming tiles
+// (max_dense > 0 in launch_ffn_mix and launch_ffn_down). dense_rows() chooses.
 constexpr int kDenseMinRows = kItemRows + 1;
-constexpr int kDenseRows = 256;
-__host__ __device__ inline int dense_items(int rows) { return (rows + kDenseRows - 1) / kDenseRows; }
-__host__ __device__ inline int dense_item_rows(int rows) {
-  const int m = dense_items(rows);
+constexpr int kDenseRowsLarge = 256;
+constexpr int kDenseRowsSmall = 128;
+constexpr int kDenseRideHidden = 1024;   // least hidden size of the riding tiles
+__host__ __device__ inline int dense_items(int rows, int R) { return (rows + R - 1) / R; }
+__host__ __device__ inline int dense_item_rows(int rows, int R) {
+  const int m = dense_items(rows, R);
   return 32 * (((rows + m - 1) / m + 31) / 32);
 }
-// Cost of one tile in the split of a launch's tiles over the XCDs: its row
-// tiles of 32 plus a constant part. Bounded by kDenseCostMax; an expert with
-// kDenseMinRows rows or more costs at least kDenseCostMin per tile.
+// Bound on the items of the dense experts of `routes` routes: an item holds
+// more than kDenseMinRows - 1 rows on average, and an expert one partly
+// filled item at most.
+inline int64_t dense_items_max(int64_t routes, int E, int R) {
+  const int64_t a = 2 * routes / (2 * kDenseMinRows - 1), b = routes / R + E;
+  return a < b ? a : b;
+}
+// Cost of an expert's tiles in the split of a launch's tiles over the XCDs,
+// per feature tile: kDenseCostBase an item and 1 for each 32 rows. The planning
+// counts a tile as the expert's cost over its items, rounded down: at least
+// kDenseCostMin (129 rows in two items), and at most dense_cost_max(R).
 constexpr int kDenseCostBase = 8;
-constexpr int kDenseCostMin = kDenseCostBase + (kDenseMinRows + 31) / 32;
-constexpr int kDenseCostMax = kDenseCostBase + kDenseRows / 32;
+constexpr int kDenseCostMin = kDenseCostBase + 2;
+__host__ __device__ constexpr int dense_cost_max(int R) { return kDenseCostBase + R / 32 + 1; }
 hipError_t launch_ffn_dense(bool up, const FfnLaunch& a, hipEvent_t ev0, hipEvent_t ev1,
                             hipStream_t s);
 

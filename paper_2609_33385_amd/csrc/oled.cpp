@@ -56,6 +56,7 @@ using oled::WorkItem;
 thread_local std::string g_create_error;
 
 constexpr int kFetchBlocks = 64;    // workgroups of a launch that copy misses (multiple of 8)
+static_assert(oled::kDenseRowsSmall == 1 << 7 && oled::kDenseRowsLarge == 1 << 8, "dense_shift");
 constexpr int kMissGridCap = 256;   // GEMM workgroups of a miss launch (they loop over tiles)
 
 enum class Stage { kIdle, kRouted, kHitsQueued, kApplied };
@@ -66,6 +67,7 @@ struct OpRec {
   int part;               // 0 gate/up, 1 down, 2 hit down + miss gate/up, 3 dense gate/up,
                           // 4 dense down, -1 other
   bool hits;              // hit-expert launch (else miss launch)
+  bool dense;             // dense tiles ride in it (gate/up with part 2, down with part 1)
   int64_t bytes, flops, h2d;
   hipEvent_t a, b;
 };
@@ -153,7 +155,8 @@ struct Ctx {
   // the layer in flight
   Stage stage = Stage::kIdle;
   int cur_layer = -1, cur_T = 0, cur_route = 0;
-  bool cur_dense = false;          // the layer in flight has dense items
+  bool cur_dense = false;          // the layer in flight may have dense items
+  int cur_dense_rows = 0;          // and their most rows (kDenseRowsSmall: they ride)
   hipStream_t cur_stream = nullptr;
   bool have_stream = false;
   const void* fwd_x = nullptr;
@@ -547,6 +550,10 @@ void complete_op(const Ctx* c, OpRec& op, const RouteStats& r) {
     const Part h = streamed(r, true), m = streamed(r, false);
     op.bytes = down_bytes(c, h.n, h.rows) + up_bytes(c, m.n, m.rows);
     op.flops = down_flops(c, h.rows) + up_flops(c, m.rows);
+    if (op.dense) {
+      op.bytes += up_bytes(c, r.n_dense, r.dense_rows);
+      op.flops += up_flops(c, r.dense_rows);
+    }
     if (op.h2d < 0) op.h2d = static_cast<int64_t>(r.n_staged) * (c->eb - c->e13);
     return;
   }
@@ -567,6 +574,10 @@ void complete_op(const Ctx* c, OpRec& op, const RouteStats& r) {
   } else {
     op.bytes = down_bytes(c, n, rows);
     op.flops = down_flops(c, rows);
+    if (op.dense) {
+      op.bytes += down_bytes(c, r.n_dense, r.dense_rows);
+      op.flops += down_flops(c, r.dense_rows);
+    }
     if (op.h2d < 0) op.h2d = static_cast<int64_t>(r.n_staged) * (c->eb - c->e13);
   }
 }
@@ -652,6 +663,18 @@ oled_status check_slots(Ctx* c) {
 }
 
 
+// Rows of the dense items of a block of T tokens. With the shader transfer,
+// up to 512 routes per expert on average, small tiles ride in the streaming
+// launches (see k_ffn_mix); beyond, and where the host enqueues the misses'
+// GEMMs by itself, large tiles in launches of their own. 3001 tokens x 64
+// experts (375 a head): the large tiles alone 231 + 147 us, the small ones 225
+// + 136; 16384 tokens x 128 (1024 a head): 2.85 + 1.80 ms against 2.97 + 1.87.
+int dense_rows(const Ctx* c, int T) {
+  const bool ride = c->copy_mode == OLED_COPY_SHADER && !c->coop && c->H >= oled::kDenseRideHidden &&
+                    static_cast<int64_t>(T) * c->K <= static_cast<int64_t>(512) * c->E;
+  return ride ? oled::kDenseRowsSmall : oled::kDenseRowsLarge;
+}
+
 // Streaming work items of at most n_exp experts of the layer in flight: one
 // each where no expert has more rows than an item (blocks of at most
 // kItemRows tokens, and blocks whose larger experts run as dense tiles). It
@@ -713,11 +736,8 @@ oled_status launch_hits(Ctx* c, int layer, hipStream_t s, int64_t h2d) {
 // item counts are on the device.
 oled_status launch_dense(Ctx* c, int layer, hipStream_t s) {
   const int64_t routes = static_cast<int64_t>(c->cur_T) * c->K;
-  // dense_items over the experts with at least kDenseMinRows rows: an item
-  // holds at least that many rows, and an expert at most one short item
-  const int max_items = static_cast<int>(
-      std::min<int64_t>(routes / oled::kDenseMinRows, routes / oled::kDenseRows + c->E));
-  FfnLaunch a = ffn_args(c, layer, 0, max_items, 0);
+  FfnLaunch a = ffn_args(c, layer, 0, 0, 0);
+  a.max_dense = static_cast<int>(oled::dense_items_max(routes, c->E, oled::kDenseRowsLarge));
   a.dense_tab = c->d_dense_tab;
   a.src = c->fwd_x;
   a.src_bytes = static_cast<int64_t>(c->cur_T) * c->H * 2;
@@ -995,26 +1015,44 @@ oled_status launch_shader_rest(Ctx* c, int layer, hipStream_t s, int64_t h2d) {
   d.fetch.len = c->eb - c->e13;
   FfnLaunch u = ffn_args(c, layer, 1, max_miss_items, kMissGridCap);
   u.src = c->fwd_x;
+  const bool ride = c->cur_dense && c->cur_dense_rows == oled::kDenseRowsSmall;
+  const int64_t routes = static_cast<int64_t>(c->cur_T) * c->K;
+  const int max_dense =
+      ride ? static_cast<int>(oled::dense_items_max(routes, c->E, oled::kDenseRowsSmall)) : 0;
+  if (ride) {
+    u.dense_tab = c->d_dense_tab;
+    u.dense_start = c->d_dense_start;
+    u.src_bytes = static_cast<int64_t>(c->cur_T) * c->H * 2;
+    u.max_dense = max_dense;
+  }
   {
     OpEvents ev = op_begin(c, OLED_OP_FFN_DOWN);
     HIP_TRY(c, oled::launch_ffn_mix(bf16, d, u, ev.a, ev.b, s));
     OpRec o = rec(OLED_OP_FFN_DOWN, layer, -1);
     o.route_seq = c->cur_route;
     o.part = 2;
+    o.dense = ride;
     o.h2d = h2d >= 0 ? h2d - h2d * c->e13 / c->eb : -1;
     op_end(c, ev, o);
   }
   FfnLaunch a = ffn_args(c, layer, 1, max_miss_items, kMissGridCap);
   a.src = c->d_h;
+  if (ride) {
+    a.dense_tab = c->d_dense_tab;
+    a.dense_start = c->d_dense_start + 9;
+    a.src_bytes = routes * c->I * 2;
+    a.max_dense = max_dense;
+  }
   {
     OpEvents ev = op_begin(c, OLED_OP_FFN_DOWN);
     HIP_TRY(c, oled::launch_ffn_down(bf16, a, ev.a, ev.b, s));
     OpRec o = rec(OLED_OP_FFN_DOWN, layer, -1);
     o.route_seq = c->cur_route;
     o.part = 1;
+    o.dense = ride;
     op_end(c, ev, o);
   }
-  return c->cur_dense ? launch_dense(c, layer, s) : OLED_OK;
+  return c->cur_dense && !ride ? launch_dense(c, layer, s) : OLED_OK;
 }
 
 }  // namespace
@@ -1117,7 +1155,7 @@ oled_status oled_create(const oled_config* cfg, void** ctx_out) {
   c->dense_ok = c->dtype == OLED_BF16 && c->H % 256 == 0 && c->I % 256 == 0 &&
                 c->Tmax >= oled::kDenseMinRows && routes * c->I * 2 <= INT32_MAX &&
                 static_cast<int64_t>(c->Tmax) * c->H * 2 <= INT32_MAX &&
-                static_cast<int64_t>(oled::kDenseRows) * c->H * 4 <= INT32_MAX;
+                static_cast<int64_t>(oled::kDenseRowsLarge) * c->H * 4 <= INT32_MAX;
   c->host_pool = static_cast<const char*>(cfg->host_pool);
   c->P = cfg->host_pool_blocks;
   c->host_block_of.assign(cfg->host_block_of, cfg->host_block_of + nb);
@@ -1305,6 +1343,8 @@ oled_status route_impl(Ctx* c, int32_t layer, const float* logits_dev, int32_t T
   o.dense_min = c->dense_ok && T >= oled::kDenseMinRows ? oled::kDenseMinRows : 0;
   o.dense_tab = c->d_dense_tab;
   o.dense_start = c->d_dense_start;
+  const int drows = dense_rows(c, T);
+  o.dense_shift = drows == oled::kDenseRowsSmall ? 7 : 8;
   o.dense_nf[0] = c->I / 128;
   o.dense_nf[1] = c->H / 256;
   o.ring = c->d_ring;
@@ -1344,6 +1384,7 @@ oled_status route_impl(Ctx* c, int32_t layer, const float* logits_dev, int32_t T
   c->cur_layer = layer;
   c->cur_T = T;
   c->cur_dense = o.dense_min > 0;
+  c->cur_dense_rows = drows;
   c->cur_stream = s;
   c->have_stream = true;
   c->fwd_x = nullptr;

@@ -532,8 +532,8 @@ __device__ __forceinline__ void rank_chunk(const int32_t* idx, int t0, int t1, i
 }
 
 // Cost of an expert's dense tiles per feature tile (see kDenseCostBase).
-__device__ __forceinline__ int dense_cost(int rows) {
-  return dense_items(rows) * (kDenseCostBase + dense_item_rows(rows) / 32);
+__device__ __forceinline__ int dense_cost(int rows, int shift) {
+  return ((rows + (1 << shift) - 1) >> shift) * kDenseCostBase + ((rows + 31) >> 5);
 }
 
 // Histogram, offsets, work list and stable permutation of the T*k routes in
@@ -571,6 +571,7 @@ __device__ __forceinline__ void permute_body(const int32_t* idx, int T, int k, i
   const int E = o.E, layer = o.layer;
   const int R = T * k;
   const bool cache = o.cv.hdr != nullptr;   // else routing and permutation only
+  const int dsh = o.dense_shift;
   for (int e = tid; e < kMaxExperts; e += nthr) s_cnt[e] = 0;
   __syncthreads();
   // Chunked: counts per chunk in chunk_base [n_chunks][E], from an earlier
@@ -622,8 +623,8 @@ __device__ __forceinline__ void permute_body(const int32_t* idx, int T, int k, i
       dn[q] = o.dense_min > 0 && c[q] >= o.dense_min;
       nh[q] = hit[q] && !dn[q] ? ni : 0;
       nm[q] = miss[q] && !dn[q] ? ni : 0;
-      sdi += dn[q] ? dense_items(c[q]) : 0;
-      sdc += dn[q] ? dense_cost(c[q]) : 0;
+      sdi += dn[q] ? (c[q] + (1 << dsh) - 1) >> dsh : 0;
+      sdc += dn[q] ? dense_cost(c[q], dsh) : 0;
       n_dense += dn[q] ? 1 : 0;
       n_dhit += dn[q] && hit[q] ? 1 : 0;
       drows += dn[q] ? c[q] : 0;
@@ -696,8 +697,8 @@ __device__ __forceinline__ void permute_body(const int32_t* idx, int T, int k, i
       xh += nh[q];
       xm += nm[q];
       xx += miss[q] ? 1 : 0;
-      xdi += dn[q] ? dense_items(c[q]) : 0;
-      xdc += dn[q] ? dense_cost(c[q]) : 0;
+      xdi += dn[q] ? (c[q] + (1 << dsh) - 1) >> dsh : 0;
+      xdc += dn[q] ? dense_cost(c[q], dsh) : 0;
       xdn += dn[q] ? 1 : 0;
     }
     // this iteration's transferred misses, for the next one: expert e = 4 lane + q
@@ -767,16 +768,16 @@ __device__ __forceinline__ void permute_body(const int32_t* idx, int T, int k, i
       o.dense_tab[s_dexp[e]] = DenseExpert{s_dfirst[e], s_off[e], c | (e << 16), hslot};
       // the tiles in expert order cost dense_cost(c) per feature tile: the
       // XCD boundaries (eighths of the whole) that fall in this expert's
-      // (32 bits: at most 4352 items, kDenseCostMax each, times 8191 feature
-      // tiles; 64-bit divisions here cost the planning 5 us)
-      const uint32_t mine = dense_cost(c), tile = mine / dense_items(c);
+      // (32 bits: at most 8448 items of cost 13, or 4352 of 17, times 8191
+      // feature tiles; 64-bit divisions here cost the planning 5 us)
+      const uint32_t mine = dense_cost(c, dsh), m = (c + (1 << dsh) - 1) >> dsh, tile = mine / m;
 #pragma unroll
       for (int p = 0; p < 2; ++p) {
         const uint32_t nf = o.dense_nf[p], lo = s_dcost[e] * nf, len = mine * nf;
         const uint32_t eighth = static_cast<uint32_t>(s_stat[15]) * nf / 8;
         for (uint32_t x = 0; x < 8; ++x)
           if (eighth * x - lo < len)   // unsigned: lo <= eighth * x < lo + len
-            o.dense_start[9 * p + x] = s_dfirst[e] * nf + (eighth * x - lo) / tile;
+            o.dense_start[9 * p + x] = s_dfirst[e] * nf + min((eighth * x - lo) / tile, m * nf);
       }
       continue;
     }

@@ -1,7 +1,8 @@
 """The split of the dense-tile launches: experts whose routed rows sit at the
-edges of the streaming / dense threshold, of the 32-row tiles and of the
+edges of the streaming / dense threshold, of the 32-row tiles and of the 128- and
 256-row items, and one expert that holds nearly every row, so that the ranges
-of tiles per XCD are as uneven as they get.
+of tiles per XCD are as uneven as they get. At hidden 1024 and above the small
+tiles ride in the streaming launches (up to 512 routes per expert on average).
 
 k = 1 makes every gate 1 and every expert's rows exactly the tokens sent to
 it. Every output row is checked against the oracle in float64; the bound is
@@ -26,7 +27,7 @@ SPLITS = {
 }
 
 
-@pytest.mark.parametrize("H,I", [(256, 256), (768, 512)])
+@pytest.mark.parametrize("H,I", [(256, 256), (768, 512), (1024, 256), (1024, 2048)])
 @pytest.mark.parametrize("name", SPLITS)
 def test_dense_split(name, H, I):
     rows = SPLITS[name]
