@@ -22,11 +22,6 @@ constexpr int kThreads = 256;
 constexpr int kScoreRoutes = 8192;         // routes per scoring workgroup of a large block
 constexpr int kScoreRoutesSingle = 8192;   // up to this many routes one workgroup scores
 
-__device__ __forceinline__ bool ranks_above(unsigned long long sa, bool ra, int a,
-                                            unsigned long long sb, bool rb, int b) {
-  return sa > sb || (sa == sb && (ra > rb || (ra == rb && a < b)));
-}
-
 // Folds the layer's last routing into its smoothed statistics (Sec. 4.3):
 // activation ratio |A| / E and utilisation hits / C, moving averages with
 // weight 1/2 on the newest value (float64; halving is exact, so a fused
@@ -129,17 +124,23 @@ __device__ __forceinline__ void score_commit(const ScoreArgs& a, unsigned long l
   RetainOut* __restrict__ out = a.out;
   __shared__ uint32_t s_rc[kMaxExperts];  // bit 1: previously resident, bit 0: candidate
   __shared__ int32_t s_rank[kMaxExperts];
+  // The ranking's keys, 16 bytes at a time: a candidate's retention key and
+  // its place among equal keys (previously resident first, then id asc, as a
+  // number from 1 up); 0 and 0 for the others, which rank above nothing.
+  __shared__ __align__(16) unsigned long long s_ck[kMaxExperts];
+  __shared__ __align__(16) uint32_t s_tie[kMaxExperts];
   const uint32_t* s_res = st.res;
   const uint32_t* s_cpu = st.cpu;
   const int tid = threadIdx.x;
-  for (int e = tid; e < kMaxExperts; e += kThreads) {
-    s_rank[e] = 0;
-    const bool r = e < E && ((s_res[e >> 5] >> (e & 31)) & 1u);
-    const bool cpu = e < E && ((s_cpu[e >> 5] >> (e & 31)) & 1u);
-    const bool c = e < E && (r || (counts[e] > 0 && !cpu));
-    s_rc[e] = (r ? 2u : 0u) | (c ? 1u : 0u);
-  }
-  // (s_rc and s_rank are next read after the barrier that follows the keys)
+  static_assert(kThreads == kMaxExperts, "one thread per expert");
+  const bool was_res = tid < E && ((s_res[tid >> 5] >> (tid & 31)) & 1u);
+  const bool on_cpu = tid < E && ((s_cpu[tid >> 5] >> (tid & 31)) & 1u);
+  const bool cand = tid < E && (was_res || (counts[tid] > 0 && !on_cpu));
+  s_rank[tid] = 0;
+  s_rc[tid] = (was_res ? 2u : 0u) | (cand ? 1u : 0u);
+  s_tie[tid] = cand ? (was_res ? kMaxExperts : 0) + static_cast<uint32_t>(kMaxExperts - tid) : 0u;
+  s_ck[tid] = 0ull;   // unless a candidate, below
+  // (these arrays are next read after the barrier that follows the keys)
   const int s_bad = *p_bad;
   CacheHdr* hdr = cv.hdr;
   const bool commit = !s_bad && !st.route_bad && !a.reject;
@@ -152,6 +153,7 @@ __device__ __forceinline__ void score_commit(const ScoreArgs& a, unsigned long l
   for (int e = tid; e < E; e += kThreads) {
     if (cv.policy == 0) {
       s_K[e] = s_S[e];
+      if (cand) s_ck[e] = s_S[e];
       continue;
     }
     int32_t* lu = cv.last_use + static_cast<size_t>(layer) * E + e;
@@ -165,25 +167,43 @@ __device__ __forceinline__ void score_commit(const ScoreArgs& a, unsigned long l
       *fr = f;
     }
     s_K[e] = cv.policy == 1 ? static_cast<unsigned long long>(u) : f;
+    if (cand) s_ck[e] = s_K[e];
   }
-  __syncthreads();
+  const int n_cand = __syncthreads_count(cand);
   if (tid == 0 && commit && cv.policy != 0) cv.iters[layer] = it_now;
 
   // Top-C over candidates R u A by (key desc, previously resident first, id
-  // asc): rank[e] = number of candidates above e. Thread pairs (e, quarter of
-  // the candidates) count with broadcast LDS reads; LDS atomics sum the parts.
-  const int fq = (E + 3) >> 2;
-  for (int idx = tid; idx < 4 * E; idx += kThreads) {
-    const int e = idx % E, part = idx / E;
-    const unsigned long long se = s_K[e];
-    const bool re = s_rc[e] & 2u;
-    int cnt = 0;
-    const int f1 = min(E, (part + 1) * fq);
-    for (int f = part * fq; f < f1; ++f) {
-      const uint32_t rcf = s_rc[f];
-      cnt += ((rcf & 1u) && ranks_above(s_K[f], rcf & 2u, f, se, re, e)) ? 1 : 0;
+  // asc): rank[e] = number of candidates above e; nothing to rank where all of
+  // them fit (every rank stays 0). Thread pairs (e, quarter of the candidates)
+  // count with broadcast LDS reads, 8 candidates at a time so that their reads
+  // are in flight together; LDS atomics sum the parts. (One comparison at a
+  // time, each waiting for its two reads, this bound the launch: 53 us for 512
+  // tokens x 256 experts, now 12; the commit alone at 128 experts 17, now 6
+  // where all fit and 15 against 22 where 124 candidates meet 51 places.)
+  if (n_cand > C) {
+    const int fq = ((E + 31) >> 5) << 3;   // a quarter of the experts, whole groups of 8
+    for (int idx = tid; idx < 4 * E; idx += kThreads) {
+      const int e = idx % E, part = idx / E;
+      const unsigned long long se = s_ck[e];
+      const uint32_t te = s_tie[e];
+      int cnt = 0;
+      const int f1 = min(kMaxExperts, (part + 1) * fq);
+      for (int f = part * fq; f < f1; f += 8) {
+        ulonglong2 kf[4];
+        uint4 tf[2];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) kf[u] = *reinterpret_cast<const ulonglong2*>(&s_ck[f + 2 * u]);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) tf[u] = *reinterpret_cast<const uint4*>(&s_tie[f + 4 * u]);
+        const uint32_t t8[8] = {tf[0].x, tf[0].y, tf[0].z, tf[0].w, tf[1].x, tf[1].y, tf[1].z, tf[1].w};
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const unsigned long long k = (u & 1) ? kf[u >> 1].y : kf[u >> 1].x;
+          cnt += (k > se || (k == se && t8[u] > te)) ? 1 : 0;
+        }
+      }
+      atomicAdd(&s_rank[e], cnt);
     }
-    atomicAdd(&s_rank[e], cnt);
   }
   __syncthreads();
   if (tid >= 64) return;
