@@ -20,11 +20,6 @@ __device__ __forceinline__ uint32_t ord_key(float v) {
   return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
-// Median of three (the compiler emits one v_med3_u32 for this form).
-__device__ __forceinline__ uint32_t med3u(uint32_t a, uint32_t b, uint32_t c) {
-  return max(min(a, b), min(max(a, b), c));
-}
-
 __device__ __forceinline__ float ord_value(uint32_t o) {
   return __uint_as_float((o & 0x80000000u) ? (o & 0x7FFFFFFFu) : ~o);
 }
@@ -152,13 +147,17 @@ __global__ __launch_bounds__(256) void k_route_topk(const float* __restrict__ lo
 // Large blocks: one token per lane. A wavefront takes 64 tokens; their
 // logits pass through LDS 32 experts at a time (coalesced row loads, one
 // padded row per token), the next 32 already in flight while the current ones
-// are ranked. Each lane ranks its token's experts by a packed 32-bit key: the
-// top 24 bits of the order-preserving logit key, then 255 - id, so that one
-// max / min pair per list position inserts (a bubble network over KP >= k + 1
-// positions). Where the k + 1 best packed keys differ in their top 24 bits,
-// their order is the exact (logit desc, id asc) order and the first k are the
-// routes; where two of them share those bits the whole wavefront ranks that
-// token again from memory with full keys (wave_topk_ids). Gates as in route_token (fp64 exp of
+// are ranked. Each lane ranks its token's experts by a packed key, compared as
+// a float: the top 24 bits of the logit (its class), then the id, so that one
+// median per list position inserts (a bubble network over KP >= k + 1
+// positions). Where the k + 1 best keys are of different classes (those of +0
+// and -0 counting as one), their order is the exact (logit desc, id asc) order
+// and the first k are the routes; where two of them share a class, or a logit
+// is not finite, the whole wavefront ranks that token again from memory with
+// full keys (wave_topk_ids).
+// What bounds it on large batches: the vector instructions of the insertion,
+// KP + 2 a logit (a float median orders the logit's own bits, and one
+// multiply-add checks it; ordering integer keys took KP + 9). Gates as in route_token (fp64 exp of
 // l_j - l_0, sum in slot order, one rounding to fp32), from the logits re-read
 // by expert id.
 constexpr int kLaneChunk = 32;
@@ -231,6 +230,43 @@ __device__ __forceinline__ void lds_wait_all(uint32_t (&v)[N]) {
   for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i]));
 }
 
+// Adds logit x of expert e to a token's descending list of packed keys.
+template <int KP>
+__device__ __forceinline__ void insert_key(float (&key)[KP], float& zeros, float x, int e) {
+  zeros = __builtin_fmaf(x, 0.f, zeros);
+  const float c = __uint_as_float((__float_as_uint(x) & 0xFFFFFF00u) | static_cast<uint32_t>(e));
+  // insertion into the descending list: new[q] = max(old[q], min(old[q-1], c)),
+  // the median of (old[q-1], old[q], c) since old[q-1] >= old[q]: one
+  // v_med3_f32 per position, every position from the old list
+#pragma unroll
+  for (int q = KP - 1; q >= 1; --q) key[q] = __builtin_amdgcn_fmed3f(key[q - 1], key[q], c);
+  key[0] = __builtin_amdgcn_fmed3f(key[0], c, __builtin_inff());
+}
+
+// Keys of one class: the same top 24 bits, or both within the zero classes.
+__device__ __forceinline__ bool same_class(float a, float b) {
+  const uint32_t u = __float_as_uint(a), v = __float_as_uint(b);
+  return ((u ^ v) >> 8) == 0u || (((u | v) << 1) >> 9) == 0u;
+}
+
+// Gates of a token from the logits of its routes: fp64 exp of l_j - l_0,
+// summed in slot order, one rounding to fp32.
+template <int KM>
+__device__ __forceinline__ void write_token_gates(const float (&lv)[KM], int k,
+                                                  float* __restrict__ out) {
+  double ex[KM];
+  double sum = 0.0;
+#pragma unroll
+  for (int j = 0; j < KM; ++j) {
+    const double d = static_cast<double>(lv[j]) - static_cast<double>(lv[0]);
+    ex[j] = j == 0 ? 1.0 + d : (j < k ? exp(d) : 0.0);   // d is 0 (or not a number) for j = 0
+    if (j < k) sum += ex[j];
+  }
+#pragma unroll
+  for (int j = 0; j < KM; ++j)
+    if (j < k) out[j] = static_cast<float>(ex[j] / sum);
+}
+
 // DMA streaming (E % 32 == 0, the rows within a 32-bit byte offset): each
 // wavefront ranks several blocks of 64 tokens in turn, its logits copied into
 // LDS 32 experts (128 bytes per row) at a time by LDS DMA, two chunks in
@@ -251,54 +287,32 @@ __global__ __launch_bounds__(256) void k_route_lanes(const float* __restrict__ l
   static_assert(KP > KM, "the packed list holds the k-th and the (k+1)-th key");
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  uint32_t key[KP];
-  int nonfinite = 0;
+  float key[KP];
+  float zeros = 0.f;   // sum of 0 * logit: not a number once a logit is non-finite
   auto reset = [&]() {
 #pragma unroll
-    for (int j = 0; j < KP; ++j) key[j] = 0u;
-    nonfinite = 0;
+    for (int j = 0; j < KP; ++j) key[j] = -__builtin_inff();
+    zeros = 0.f;
   };
-  auto insert = [&](float x, int e) {
-    nonfinite |= !__builtin_isfinite(x);
-    const uint32_t c = (max(ord_key(x), 1u) & 0xFFFFFF00u) | static_cast<uint32_t>(255 - e);
-    // insertion into the descending list: new[q] = max(old[q], min(old[q-1], c)),
-    // the median of (old[q-1], old[q], c) since old[q-1] >= old[q]: one
-    // v_med3_u32 per position, every position from the old list
-#pragma unroll
-    for (int q = KP - 1; q >= 1; --q) key[q] = med3u(key[q - 1], key[q], c);
-    key[0] = max(key[0], c);
-  };
+  auto insert = [&](float x, int e) { insert_key<KP>(key, zeros, x, e); };
   // ids of the block at t0 from the lanes' keys: where two of the k + 1 best
-  // share their top 24 bits, the whole wavefront ranks that token again from
-  // memory with full keys
+  // share a class, or a logit is non-finite, the whole wavefront ranks that
+  // token again from memory with full keys
   auto block_ids = [&](int t0, int32_t (&id)[KM]) {
     const int t = t0 + lane;
     bool amb = false;
     if (t < T) {
+      amb = zeros != zeros;
 #pragma unroll
       for (int j = 0; j + 1 < KP; ++j)
-        if (j < k) amb |= (key[j] >> 8) == (key[j + 1] >> 8);
+        if (j < k) amb |= same_class(key[j], key[j + 1]);
     }
 #pragma unroll
-    for (int j = 0; j < KM; ++j) id[j] = 255 - static_cast<int>(key[j] & 0xFFu);
+    for (int j = 0; j < KM; ++j) id[j] = static_cast<int>(__float_as_uint(key[j]) & 0xFFu);
     for (uint64_t todo = __ballot(amb); todo != 0ull; todo &= todo - 1) {
       const int owner = __builtin_ctzll(todo);
       wave_topk_ids<KM>(logits + static_cast<size_t>(t0 + owner) * E, E, k, lane == owner, id);
     }
-  };
-  // gates of token t from the logits of its routes: fp64 exp of l_j - l_0,
-  // summed in slot order, one rounding to fp32
-  auto write_gates = [&](const float (&lvf)[KM], int t) {
-    double ex[KM];
-    double sum = 0.0;
-#pragma unroll
-    for (int j = 0; j < KM; ++j) {
-      ex[j] = j < k ? exp(static_cast<double>(lvf[j]) - static_cast<double>(lvf[0])) : 0.0;
-      if (j < k) sum += ex[j];
-    }
-#pragma unroll
-    for (int j = 0; j < KM; ++j)
-      if (j < k) gates[static_cast<size_t>(t) * k + j] = static_cast<float>(ex[j] / sum);
   };
   if constexpr (DMA) {
     __shared__ u32x4r_t s_dma[4][2][64 * 8];   // [wavefront][buffer][token][slot]: 64 KiB
@@ -346,7 +360,7 @@ __global__ __launch_bounds__(256) void k_route_lanes(const float* __restrict__ l
       float lvf[KM];
 #pragma unroll
       for (int j = 0; j < KM; ++j) lvf[j] = __uint_as_float(lvu[j]);
-      if (pt < T) write_gates(lvf, pt);
+      if (pt < T) write_token_gates<KM>(lvf, k, gates + static_cast<size_t>(pt) * k);
     };
     for (int g = 0; g < total; ++g) {
       const int bi = g / nch, c = g - bi * nch;
@@ -385,7 +399,7 @@ __global__ __launch_bounds__(256) void k_route_lanes(const float* __restrict__ l
 #pragma unroll
           for (int j = 0; j < KM; ++j)
             if (j < k) topk_idx[static_cast<size_t>(t) * k + j] = id[j];
-          if (nonfinite) atomicOr(&bad_flag[t / Tb], 1);   // token t's block
+          if (zeros != zeros) atomicOr(&bad_flag[t / Tb], 1);   // token t's block
         }
         if (pend) finish();   // the last block's logits have landed
         // this block's route logits for its gates, loaded with KM lanes per
@@ -455,8 +469,167 @@ __global__ __launch_bounds__(256) void k_route_lanes(const float* __restrict__ l
 #pragma unroll
       for (int j = 0; j < KM; ++j)
         if (j < k) topk_idx[static_cast<size_t>(t) * k + j] = id[j];
-      write_gates(lv, t);
-      if (nonfinite) atomicOr(&bad_flag[t / Tb], 1);   // token t's block
+      write_token_gates<KM>(lv, k, gates + static_cast<size_t>(t) * k);
+      if (zeros != zeros) atomicOr(&bad_flag[t / Tb], 1);   // token t's block
+    }
+  }
+}
+
+// DPP controls that pair lane i with lane i ^ 1 and i ^ 2 of its quad, and with
+// lane 7 - i of its 8 (the quads hold equal lists by then).
+template <int STEP>
+__device__ __forceinline__ float dpp_pair(float v) {
+  constexpr int kCtrl = STEP == 0 ? 0xB1 : (STEP == 1 ? 0x4E : 0x141);
+  const int b = static_cast<int>(__float_as_uint(v));
+  return __uint_as_float(static_cast<uint32_t>(
+      __builtin_amdgcn_update_dpp(b, b, kCtrl, 0xf, 0xf, false)));
+}
+
+// Merges this lane's descending list with its partner's and keeps the KP
+// largest in descending order (KP - 1 a power of two). max(a[i], b[KP-1-i]) are
+// the KP largest, falling and then rising; one exchange of the ends and a
+// bitonic merge of the other KP - 1 sort them.
+template <int KP, int STEP>
+__device__ __forceinline__ void merge_pair(float (&key)[KP]) {
+  const float inf = __builtin_inff();
+  float b[KP];
+#pragma unroll
+  for (int j = 0; j < KP; ++j) b[j] = dpp_pair<STEP>(key[j]);
+#pragma unroll
+  for (int j = 0; j < KP; ++j) key[j] = __builtin_amdgcn_fmed3f(key[j], b[KP - 1 - j], inf);
+  auto exchange = [&](int i, int j) {
+    const float hi = __builtin_amdgcn_fmed3f(key[i], key[j], inf);
+    key[j] = __builtin_amdgcn_fmed3f(key[i], key[j], -inf);
+    key[i] = hi;
+  };
+  exchange(0, KP - 1);
+#pragma unroll
+  for (int d = (KP - 1) / 2; d >= 1; d >>= 1)
+#pragma unroll
+    for (int i = 1; i + d < KP; ++i)
+      if (((i - 1) & d) == 0) exchange(i, i + d);
+}
+
+// Large batches of E = 32 G experts (G = 1, 2, 4 or 8): as the streamed form
+// above, with G lanes per token. A chunk is 64 / G whole rows, 8 KiB of
+// contiguous logits: lane G t + p ranks experts 32 p .. 32 p + 31 of row t, then
+// the G lists of a row are merged. The logits of the routes are then still in
+// LDS. With one lane per token and the row in G chunks they had to be read
+// again for the gates, nearly every line of the row and long after it had left
+// L2: twice the bytes of the logits, which bounded the launch. The gates are
+// computed when 64 tokens are ranked, one token per lane.
+// Measured at 32 blocks of 65535 tokens x 128 experts, k = 8: 342 ->
+// 279 us (the whole call with the permutation and priority sums 416 -> 354).
+template <int KP, int KM, int G>
+__global__ __launch_bounds__(256) void k_route_rows(const float* __restrict__ logits, int T, int k,
+                                                    int32_t* __restrict__ topk_idx,
+                                                    float* __restrict__ gates,
+                                                    int32_t* __restrict__ bad_flag, int Tb) {
+  static_assert(KP == KM + 1, "the packed list holds the k-th and the (k+1)-th key");
+  constexpr int E = 32 * G;
+  constexpr int kRows = 64 / G;                  // tokens per chunk
+  constexpr int M = KM >= G ? KM / G : 1;        // routes a lane hands on
+  __shared__ u32x4r_t s_dma[4][2][64 * 8];       // [wavefront][buffer][32 logits][slot]: 64 KiB
+  __shared__ uint32_t s_tbl[4][64 * KM];         // per wavefront: [token][slot] route logits
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int part = lane % G;
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(logits), 0, T * E * 4, kRouteBufferFlags);   // rows past T read 0
+  const int r8 = lane >> 3, s8 = lane & 7;
+  const int stride = static_cast<int>(gridDim.x) * 4;   // blocks of 64 tokens per grid step
+  const int blk0 = static_cast<int>(blockIdx.x) * 4 + wave;
+  const int nblk = (T + 63) >> 6;
+  const int total = (blk0 < nblk ? (nblk - 1 - blk0) / stride + 1 : 0) * G;   // chunks
+  auto dma = [&](int g) {   // 32 logits 8 i + r8 of the chunk, 16-byte slots rotated as above
+    const int voff = (blk0 + g / G * stride) * (64 * E * 4) + (g % G) * 8192 + r8 * 128 +
+                     16 * (s8 ^ r8);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rs, (__attribute__((address_space(3))) void*)(&s_dma[wave][g & 1][64 * i]), 16,
+          voff + 1024 * i, 0, 0, 0);
+  };
+  const uint32_t buf0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(&s_dma[wave][0][0]));
+  const uint32_t tbl = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(&s_tbl[wave][0]));
+  if (total > 0) dma(0);
+  if (total > 1) dma(1);
+  for (int g = 0; g < total; ++g) {
+    const int c = g % G;
+    const int t0 = (blk0 + g / G * stride) * 64;   // the block's first token
+    // issued after DMA(g): DMA(g + 1), 8 loads (and stores, which only make
+    // the wait longer)
+    if (g + 1 < total) route_wait_vmcnt<8>();
+    else route_wait_vmcnt<0>();
+    asm volatile("" ::: "memory");
+    const uint32_t buf = buf0 + static_cast<uint32_t>(g & 1) * 8192u;
+    u32x4r_t x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = lds_read16r(buf + 128u * lane + 16u * (j ^ s8));
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]),
+                   "+v"(x[6]), "+v"(x[7])::"memory");
+    float key[KP];
+    float zeros = 0.f;   // sum of 0 * logit: not a number once a logit is non-finite
+#pragma unroll
+    for (int j = 0; j < KP; ++j) key[j] = -__builtin_inff();
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        insert_key<KP>(key, zeros, __uint_as_float(x[j][q]), 32 * part + 4 * j + q);
+    if constexpr (G >= 2) { merge_pair<KP, 0>(key); zeros += dpp_pair<0>(zeros); }
+    if constexpr (G >= 4) { merge_pair<KP, 1>(key); zeros += dpp_pair<1>(zeros); }
+    if constexpr (G >= 8) { merge_pair<KP, 2>(key); zeros += dpp_pair<2>(zeros); }
+    const int row = lane / G;
+    const int t = t0 + c * kRows + row;
+    const bool bad = zeros != zeros;
+    bool amb = bad;
+#pragma unroll
+    for (int j = 0; j + 1 < KP; ++j)
+      if (j < k) amb |= same_class(key[j], key[j + 1]);
+    int32_t id[KM];
+#pragma unroll
+    for (int j = 0; j < KM; ++j) id[j] = static_cast<int>(__float_as_uint(key[j]) & 0xFFu);
+    for (uint64_t todo = __ballot(amb && t < T && part == 0); todo != 0ull; todo &= todo - 1) {
+      const int owner = __builtin_ctzll(todo) / G;
+      wave_topk_ids<KM>(logits + static_cast<size_t>(t0 + c * kRows + owner) * E, E, k,
+                        row == owner, id);
+    }
+    // routes M part .. M part + M - 1 of the row: their ids go out, their logits
+    // into the table (a slot past k holds any of the row's logits)
+    int32_t mine[M];
+    uint32_t lv[M];
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      mine[m] = id[m];
+#pragma unroll
+      for (int p = 1; p < G; ++p)
+        if (M * p + m < KM && part == p) mine[m] = id[M * p + m];
+      const int e = mine[m] & (E - 1);
+      const int seg = G * row + (e >> 5);
+      lv[m] = lds_read4r(buf + 128u * seg + 16u * (((e >> 2) & 7) ^ (seg & 7)) + 4u * (e & 3));
+    }
+    lds_wait_all(lv);
+    if (g + 2 < total) dma(g + 2);   // into the buffer just read
+    const bool on = M * part < KM;
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      const int j = M * part + m;
+      if (on) lds_write4r(tbl + 4u * (KM * (c * kRows + row) + j), lv[m]);
+      if (on && j < k && t < T) topk_idx[static_cast<size_t>(t) * k + j] = mine[m];
+    }
+    if (bad && part == 0 && t < T) atomicOr(&bad_flag[t / Tb], 1);   // token t's block
+    if (c == G - 1) {   // 64 tokens are ranked
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      uint32_t lu[KM];
+#pragma unroll
+      for (int j = 0; j < KM; ++j) lu[j] = lds_read4r(tbl + 4u * (KM * lane + j));
+      lds_wait_all(lu);
+      float lvf[KM];
+#pragma unroll
+      for (int j = 0; j < KM; ++j) lvf[j] = __uint_as_float(lu[j]);
+      if (t0 + lane < T) write_token_gates<KM>(lvf, k, gates + static_cast<size_t>(t0 + lane) * k);
     }
   }
 }
@@ -1616,6 +1789,14 @@ hipError_t launch_route_topk(const float* logits, int T, int E, int k, int32_t* 
     auto go = [&](auto kp, auto km) {
       constexpr int KP = decltype(kp)::value, KM = decltype(km)::value;
       if constexpr (KM <= 8) {
+        auto rows = [&](auto gg) {
+          hipExtLaunchKernelGGL(k_route_rows<KP, KM, decltype(gg)::value>, dim3(grid), dim3(256), 0,
+                                s, ev0, ev1, 0, logits, T, k, topk_idx, gates, bad_flag, Tb);
+        };
+        if (dma && E == 32) return rows(std::integral_constant<int, 1>{});
+        if (dma && E == 64) return rows(std::integral_constant<int, 2>{});
+        if (dma && E == 128) return rows(std::integral_constant<int, 4>{});
+        if (dma && E == 256) return rows(std::integral_constant<int, 8>{});
         if (dma) {
           hipExtLaunchKernelGGL(k_route_lanes<KP, KM, true>, dim3(grid), dim3(256), 0, s, ev0,
                                 ev1, 0, logits, T, E, k, topk_idx, gates, bad_flag, Tb);
