@@ -240,6 +240,7 @@ hipError_t launch_permute_batch(const int32_t* topk_idx, int B, int T, int k,
 // last workgroup to finish routing permutes. sync: 2 device ints, zero
 // before the first launch; the kernel leaves them zero.
 bool route_fused(int T, int k);
+bool route_solo(int T, int k);   // of those, the blocks one workgroup takes alone (no sync)
 hipError_t launch_route_fused(const float* logits, int T, int k, int32_t* topk_idx, float* gates,
                               int32_t* sync, const PermuteOut& o, hipEvent_t ev0, hipEvent_t ev1,
                               hipStream_t s);
