@@ -232,6 +232,9 @@ hipError_t launch_permute_chunked(const int32_t* topk_idx, int T, int k, int32_t
 // block (routes by T*k, counts by E, offsets by E+1, bad_out by 1).
 // bad_flag: [B] non-finite flags of the top-k launch; chunk_base:
 // [B][permute_chunks(T)][E] scratch.
+// Routing and permutation of B blocks of one chunk (T <= 512), no cache: one launch.
+hipError_t launch_route_blocks(const float* logits, int B, int T, int k, int32_t* topk_idx,
+                               float* gates, const PermuteOut& o, hipStream_t s);
 hipError_t launch_permute_batch(const int32_t* topk_idx, int B, int T, int k,
                                 const int32_t* bad_flag, int32_t* chunk_base, const PermuteOut& o,
                                 hipStream_t s);
@@ -240,7 +243,6 @@ hipError_t launch_permute_batch(const int32_t* topk_idx, int B, int T, int k,
 // last workgroup to finish routing permutes. sync: 2 device ints, zero
 // before the first launch; the kernel leaves them zero.
 bool route_fused(int T, int k);
-bool route_solo(int T, int k);   // of those, the blocks one workgroup takes alone (no sync)
 hipError_t launch_route_fused(const float* logits, int T, int k, int32_t* topk_idx, float* gates,
                               int32_t* sync, const PermuteOut& o, hipEvent_t ev0, hipEvent_t ev1,
                               hipStream_t s);

@@ -444,48 +444,59 @@ __device__ __forceinline__ void merge_pair(float (&key)[KP]) {
       if (((i - 1) & d) == 0) exchange(i, i + d);
 }
 
-// Small and mid-sized blocks: a wavefront ranks four tokens, 16 lanes each. Lane
-// l of a row takes experts l, l + 16, ... (at most EPL) into a descending list
-// of packed keys, the 16 lists are merged in four steps, and lane j < k returns
-// route j: its expert (else -1) and its gate g_j = fl32(e_j / s), e_j = exp(l_j -
-// l_0) in fp64, s = e_0 + ... + e_{k-1} in slot order. The logits pass through
-// s_val (the routes' exact logits are read back by id), the exponentials through
-// s_ex, both the wavefront's own. Ties of class and non-finite logits as above;
-// *bad is set in the lanes of a row with a non-finite logit. What bounds these
-// calls is the length of the instruction stream: one token a wavefront, with a
-// wavefront maximum per route, issued three times as many instructions a token.
-template <int EPL, int KM>
-__device__ __forceinline__ int route_quad(const float* logits, int t, int T, int E, int k,
-                                          float* s_val, double* s_ex, float* gate_out, bool* bad) {
+// Small and mid-sized blocks: a wavefront ranks 64 / LPT tokens, LPT lanes each.
+// Lane l of a row takes experts l, l + LPT, ... (at most EPL) into a descending
+// list of packed keys, and the LPT lists are merged. Lane l then hands on routes
+// l, l + LPT, ... below k: emit(slot, expert, gate), g_j = fl32(e_j / s), e_j =
+// exp(l_j - l_0) in fp64, s = e_0 + ... + e_{k-1} in slot order (the exponentials
+// meet in s_ex, the wavefront's own). With 16 lanes the logits pass through s_val,
+// also the wavefront's own, where the routes' exact logits are read back by id;
+// with fewer they are read from memory again, just behind the first time. Ties of
+// class and non-finite logits as above. Returns whether the row has a non-finite
+// logit. What bounds these calls is the length of the instruction stream: one
+// token a wavefront, with a wavefront maximum per route, issued three times as
+// many instructions a token as 16 lanes, and 16 lanes three times as many as 4.
+template <int LPT, int EPL, int KM, class F>
+__device__ __forceinline__ bool route_group(const float* logits, int t, int T, int E, int k,
+                                            float* s_val, double* s_ex, F emit) {
+  static_assert((LPT == 4 || LPT == 16) && KM >= 8, "lanes of a token");
   constexpr int KP = KM + 1;
   constexpr int W = 16 * EPL;
-  const int lane = threadIdx.x & 63, l = lane & 15, row = lane >> 4;
+  constexpr int M = KM > LPT ? KM / LPT : 1;   // routes a lane hands on
+  const int lane = threadIdx.x & 63, l = lane % LPT, row = lane / LPT;
   const float* src = logits + static_cast<size_t>(min(t, T - 1)) * E;
-  float* val = s_val + row * W;
-  float x[EPL];
-#pragma unroll
-  for (int i = 0; i < EPL; ++i) x[i] = l + 16 * i < E ? src[l + 16 * i] : 0.f;
+  float* val = LPT == 16 ? s_val + row * W : nullptr;
   float key[KP];
   float zeros = 0.f;   // sum of 0 * logit: not a number once a logit is non-finite
 #pragma unroll
   for (int j = 0; j < KP; ++j) key[j] = -__builtin_inff();
+  constexpr int EB = EPL < 16 ? EPL : 16;   // loads in flight
 #pragma unroll
-  for (int i = 0; i < EPL; ++i) {
-    const int e = l + 16 * i;
-    val[e] = x[i];
-    zeros = __builtin_fmaf(x[i], 0.f, zeros);
-    insert_packed<KP>(key, e < E ? packed_key(x[i], e) : -__builtin_inff());
+  for (int i0 = 0; i0 < EPL; i0 += EB) {
+    if (i0 > 0 && LPT * i0 >= E) break;
+    float x[EB];
+#pragma unroll
+    for (int i = 0; i < EB; ++i) x[i] = l + LPT * (i0 + i) < E ? src[l + LPT * (i0 + i)] : 0.f;
+#pragma unroll
+    for (int i = 0; i < EB; ++i) {
+      const int e = l + LPT * (i0 + i);
+      if constexpr (LPT == 16) val[e] = x[i];
+      zeros = __builtin_fmaf(x[i], 0.f, zeros);
+      insert_packed<KP>(key, e < E ? packed_key(x[i], e) : -__builtin_inff());
+    }
   }
   merge_pair<KP, 0>(key);
   zeros += dpp_pair<0>(zeros);
   merge_pair<KP, 1>(key);
   zeros += dpp_pair<1>(zeros);
-  merge_pair<KP, 2>(key);
-  zeros += dpp_pair<2>(zeros);
-  merge_pair<KP, 3>(key);
-  zeros += dpp_pair<3>(zeros);
+  if constexpr (LPT == 16) {
+    merge_pair<KP, 2>(key);
+    zeros += dpp_pair<2>(zeros);
+    merge_pair<KP, 3>(key);
+    zeros += dpp_pair<3>(zeros);
+  }
   bool amb = zeros != zeros;
-  *bad = amb && t < T;
+  const bool bad = amb && t < T;
 #pragma unroll
   for (int j = 0; j + 1 < KP; ++j)
     if (j < k) amb |= same_class(key[j], key[j + 1]);
@@ -495,21 +506,37 @@ __device__ __forceinline__ int route_quad(const float* logits, int t, int T, int
   for (uint64_t todo = __ballot(amb && t < T && l == 0); todo != 0ull; todo &= todo - 1) {
     const int owner = __builtin_ctzll(todo);
     wave_topk_ids<KM>(logits + static_cast<size_t>(__builtin_amdgcn_readlane(t, owner)) * E, E, k,
-                      row == owner >> 4, id);
+                      row == owner / LPT, id);
   }
-  int mine = id[0];
+  int mine[M];
 #pragma unroll
-  for (int j = 1; j < KM; ++j)
-    if (l == j) mine = id[j];
-  wave_lds_fence();
-  const double d = static_cast<double>(val[mine & (W - 1)]) - static_cast<double>(val[id[0] & (W - 1)]);
-  const double ex = l < k ? exp(d) : 0.0;
-  s_ex[lane] = ex;
+  for (int m = 0; m < M; ++m) {
+    mine[m] = id[LPT * m < KM ? LPT * m : 0];
+#pragma unroll
+    for (int p = 1; p < LPT; ++p)
+      if (LPT * m + p < KM && l == p) mine[m] = id[LPT * m + p];
+  }
+  if constexpr (LPT == 16) wave_lds_fence();
+  auto logit = [&](int e) {   // ids past k are those of absent experts, 0
+    if constexpr (LPT == 16) return static_cast<double>(val[e & (W - 1)]);
+    else return static_cast<double>(src[min(e, E - 1)]);
+  };
+  const double v0 = logit(id[0]);
+  double* sx = s_ex + row * KM;
+  double ex[M];
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    const int j = LPT * m + l;
+    ex[m] = j < k ? exp(logit(mine[m]) - v0) : 0.0;
+    if (j < KM) sx[j] = ex[m];
+  }
   wave_lds_fence();
   double s = 0.0;
-  for (int j = 0; j < k; ++j) s += s_ex[16 * row + j];
-  *gate_out = static_cast<float>(ex / s);
-  return l < k && t < T ? mine : -1;
+  for (int j = 0; j < k; ++j) s += sx[j];
+#pragma unroll
+  for (int m = 0; m < M; ++m)
+    if (LPT * m + l < k && t < T) emit(LPT * m + l, mine[m], static_cast<float>(ex[m] / s));
+  return bad;
 }
 
 // T tokens in blocks of Tb: a non-finite logit of token t sets bad_flag[t / Tb].
@@ -519,18 +546,17 @@ __global__ __launch_bounds__(256) void k_route_topk(const float* __restrict__ lo
                                                     float* __restrict__ gates,
                                                     int32_t* __restrict__ bad_flag, int Tb) {
   __shared__ float s_val[4][64 * EPL];
-  __shared__ double s_ex[4][64];
-  const int lane = threadIdx.x & 63, l = lane & 15, wave = threadIdx.x >> 6;
+  __shared__ double s_ex[4][4 * KM];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int t0 = (blockIdx.x * 4 + wave) * 4; t0 < T; t0 += gridDim.x * 16) {
     const int t = t0 + (lane >> 4);
-    float g;
-    bool bad;
-    const int e = route_quad<EPL, KM>(logits, t, T, E, k, s_val[wave], s_ex[wave], &g, &bad);
-    if (e >= 0) {
-      topk_idx[static_cast<size_t>(t) * k + l] = e;
-      gates[static_cast<size_t>(t) * k + l] = g;
-    }
-    if (bad && l == 0) atomicOr(&bad_flag[t / Tb], 1);
+    const bool bad = route_group<16, EPL, KM>(logits, t, T, E, k, s_val[wave], s_ex[wave],
+                                              [&](int j, int e, float g) {
+                                                const size_t r = static_cast<size_t>(t) * k + j;
+                                                topk_idx[r] = e;
+                                                gates[r] = g;
+                                              });
+    if (bad && (lane & 15) == 0) atomicOr(&bad_flag[t / Tb], 1);
   }
 }
 
@@ -674,11 +700,17 @@ static_assert(kChunkTokens * kMaxTopK <= 1 << kRouteBits, "chunk-local routes fi
 static_assert(kPermThreads == 2 * kChunkTokens, "two threads per token of a chunk");
 
 constexpr int kFusedMaxRoutes = 1024;       // fused routing path: T * k routes kept in LDS
-// One workgroup routes and permutes: of 64 tokens (64 experts, k = 8) in 9.3 us
-// against 11.0 with the many-workgroup form (which clears its counters first,
-// about 1.2 us, without a context), 128 tokens in 12.7 against 13.2; 8 experts,
-// k = 2: 8.9 against 9.5 and 12.0 against 10.7.
-constexpr int kSoloMaxTokens = 64;
+// Lanes a token where one workgroup routes a block: 16 are the shorter chain, 4
+// issue a third of the instructions. 16 / 4 lanes with a context's planning: 64
+// experts, k = 8, 16, 32 and 64 tokens 7.0 / 7.6, 7.8 / 7.8 and 9.5 / 8.2 us; 128
+// experts, 64 tokens 10.1 / 9.7; 256 experts, 64 tokens 11.5 / 12.6.
+__host__ __device__ constexpr int lanes_per_token(int T, int E) {
+  return T <= 32 || (E > 64 && T <= 64) ? 16 : 4;
+}
+// Blocks that one workgroup routes and permutes (of the fused form's): 64 tokens x
+// 64 experts, k = 8, in 8.2 us against 11.0 over many workgroups, 64 x 256 in 11.5
+// against 14.2; from 96 x 128 on the two come within 1 us of each other.
+constexpr bool solo_block(int T, int E) { return T <= 64 || (E <= 64 && T <= 128); }
 // Blocks of more tokens route one token per lane, or per E / 32 lanes: fewer
 // instructions a token, but a wavefront to 64 tokens. Routing and permutation of
 // 3001 x 64, 8192 x 128 and 16384 x 128 (k = 8) with four tokens a wavefront take
@@ -1416,16 +1448,15 @@ __global__ __launch_bounds__(256) void k_route_fused(const float* __restrict__ l
   // routed (no kernel of this launch changes it before the planning step)
   if (wave == 3) prefetch_state(o.cv, E, o.layer, s_free, &s_ftop, s_res, s_pm, s_slot);
   __shared__ float s_val[4][64 * EPL];
-  __shared__ double s_ex[4][64];
+  __shared__ double s_ex[4][4 * KM];
   for (int t0 = (blockIdx.x * 4 + wave) * 4; t0 < T; t0 += gridDim.x * 16) {
     const int t = t0 + (lane >> 4);
-    float g;
-    bool bad;
-    const int e = route_quad<EPL, KM>(logits, t, T, E, k, s_val[wave], s_ex[wave], &g, &bad);
-    if (e >= 0) {
-      topk_idx[static_cast<size_t>(t) * k + (lane & 15)] = e;
-      gates[static_cast<size_t>(t) * k + (lane & 15)] = g;
-    }
+    const bool bad = route_group<16, EPL, KM>(logits, t, T, E, k, s_val[wave], s_ex[wave],
+                                              [&](int j, int e, float g) {
+                                                const size_t r = static_cast<size_t>(t) * k + j;
+                                                topk_idx[r] = e;
+                                                gates[r] = g;
+                                              });
     if (bad && (lane & 15) == 0) atomicOr(&sync[1], 1);
   }
   __threadfence();   // this workgroup's routes are visible device-wide
@@ -1445,12 +1476,12 @@ __global__ __launch_bounds__(256) void k_route_fused(const float* __restrict__ l
   permute_body(s_idx, T, k, any_bad, o, s_free, &s_ftop, s_res, s_pm, s_slot);
 }
 
-// The smallest blocks (T <= kSoloMaxTokens): routing, planning and ranking by
+// The smallest blocks (solo_block): routing, planning and ranking by
 // one workgroup of 16 wavefronts, the routes handed over in LDS. What bounds
 // these calls is the chain of latencies; the many-workgroup form above adds a
 // device-wide fence, an atomic round trip and a reload of the routes to it.
-// Routing of 32 tokens x 64 experts (k = 8): 11.3 -> 7.9 us.
-template <int EPL, int KM>
+// In a layer of 32 tokens x 64 experts (k = 8) the launch took 10.3 us, now 6.2.
+template <int LPT, int EPL, int KM>
 __global__ __launch_bounds__(kPermThreads) void k_route_solo(const float* __restrict__ logits,
                                                              int T, int k,
                                                              int32_t* __restrict__ topk_idx,
@@ -1463,29 +1494,93 @@ __global__ __launch_bounds__(kPermThreads) void k_route_solo(const float* __rest
   __shared__ int32_t s_bad;
   __shared__ uint32_t s_res[kMaxExperts / 32], s_pm[kMaxExperts / 32];
   __shared__ int32_t s_slot[kMaxExperts];
-  __shared__ float s_val[kWaves][64 * EPL];
-  __shared__ double s_ex[kWaves][64];
+  __shared__ float s_val[kWaves][LPT == 16 ? 64 * EPL : 1];
+  __shared__ double s_ex[kWaves][64 / LPT * KM];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int E = o.E;
   if (threadIdx.x == 0) s_bad = 0;
   if (wave == kWaves - 1) prefetch_state(o.cv, E, o.layer, s_free, &s_ftop, s_res, s_pm, s_slot);
   __syncthreads();
-  for (int t0 = wave * 4; t0 < T; t0 += 4 * kWaves) {
-    const int t = t0 + (lane >> 4);
-    float g;
-    bool bad;
-    const int e = route_quad<EPL, KM>(logits, t, T, E, k, s_val[wave], s_ex[wave], &g, &bad);
-    if (e >= 0) {
-      const int r = t * k + (lane & 15);
-      s_idx[r] = e;
-      topk_idx[r] = e;
-      gates[r] = g;
-    }
-    if (bad && (lane & 15) == 0) s_bad = 1;
+  for (int t0 = wave * (64 / LPT); t0 < T; t0 += 64 / LPT * kWaves) {
+    const int t = t0 + lane / LPT;
+    const bool bad = route_group<LPT, EPL, KM>(logits, t, T, E, k, s_val[wave], s_ex[wave],
+                                               [&](int j, int e, float g) {
+                                                 const int r = t * k + j;
+                                                 s_idx[r] = e;
+                                                 topk_idx[r] = e;
+                                                 gates[r] = g;
+                                               });
+    if (bad) s_bad = 1;
   }
   if (o.pub_topk) __threadfence();   // the published gates are read back at device scope
   __syncthreads();
   permute_body(s_idx, T, k, s_bad, o, s_free, &s_ftop, s_res, s_pm, s_slot);
+}
+
+// Small blocks without a cache (T <= kChunkTokens): one workgroup routes, counts
+// and ranks a block, with its routes in LDS, in one launch instead of a clearing,
+// a routing and up to three permutation launches, each bounded by its latency.
+// 16 blocks of 257 tokens x 64 experts (k = 8): 18.7 -> 10.2 us; one of 32: 11.3 ->
+// 4.9 us.
+template <int LPT, int EPL, int KM>
+__global__ __launch_bounds__(kPermThreads) void k_route_block_batch(
+    const float* __restrict__ logits, int T, int k, int32_t* __restrict__ topk_idx,
+    float* __restrict__ gates, PermuteOut o) {
+  constexpr int kWaves = kPermThreads / 64;
+  __shared__ int32_t s_idx[kChunkTokens * KM];
+  __shared__ int32_t s_cnt[kMaxExperts];
+  __shared__ int32_t s_run[kMaxExperts];
+  __shared__ int32_t s_bad;
+  __shared__ uint32_t s_mask[kMaskRows * kMaskStride];
+  __shared__ int32_t s_pre[kMaskRows * kMaskStride];
+  __shared__ float s_val[kWaves][LPT == 16 ? 64 * EPL : 1];
+  __shared__ double s_ex[kWaves][64 / LPT * KM];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int b = blockIdx.x, E = o.E;
+  const size_t R = static_cast<size_t>(T) * k;
+  logits += static_cast<size_t>(b) * T * E;
+  topk_idx += b * R;
+  gates += b * R;
+  if (tid < kMaxExperts) s_cnt[tid] = 0;
+  if (tid == 0) s_bad = 0;
+  __syncthreads();
+  for (int t0 = wave * (64 / LPT); t0 < T; t0 += 64 / LPT * kWaves) {
+    const int t = t0 + lane / LPT;
+    const bool bad = route_group<LPT, EPL, KM>(logits, t, T, E, k, s_val[wave], s_ex[wave],
+                                             [&](int j, int e, float g) {
+                                               const int r = t * k + j;
+                                               s_idx[r] = e;
+                                               topk_idx[r] = e;
+                                               gates[r] = g;
+                                               atomicAdd(&s_cnt[e], 1);
+                                             });
+    if (bad) s_bad = 1;
+  }
+  __syncthreads();
+  if (wave == 0) {   // counts and offsets, 4 experts a lane
+    int c[4], tot = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      c[q] = s_cnt[4 * lane + q];   // 0 past the last expert
+      tot += c[q];
+    }
+    const int incl = wave_incl_scan(tot);
+    int run = incl - tot;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int e = 4 * lane + q;
+      if (e < E) {
+        s_run[e] = run;
+        o.counts[static_cast<size_t>(b) * E + e] = c[q];
+        o.offsets[static_cast<size_t>(b) * (E + 1) + e] = run;
+      }
+      run += c[q];
+    }
+    if (lane == 63) o.offsets[static_cast<size_t>(b) * (E + 1) + E] = incl;
+    if (lane == 0 && o.bad_out) o.bad_out[b] = s_bad;
+  }
+  __syncthreads();
+  rank_chunk(s_idx, 0, T, k, E, T * k, s_mask, s_pre, s_run, o.perm + b * R, o.inv_perm + b * R);
 }
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
@@ -1847,9 +1942,9 @@ hipError_t launch_router_logits(bool bf16, const void* x, const void* wg, int T,
 }
 
 bool route_fused(int T, int k) { return T * k <= kFusedMaxRoutes; }
-bool route_solo(int T, int k) { return route_fused(T, k) && T <= kSoloMaxTokens; }
 
-// Calls go(EPL, KM) with the smallest form of route_quad that holds E and k.
+// Calls go(EPL, KM) with the smallest form of route_group that holds E and k: EPL
+// experts a lane with 16 lanes a token, 4 EPL with 4.
 template <class F>
 hipError_t quad_form(int E, int k, F go) {
   using std::integral_constant;
@@ -1916,6 +2011,21 @@ hipError_t launch_route_topk(const float* logits, int T, int E, int k, int32_t* 
   });
 }
 
+hipError_t launch_route_blocks(const float* logits, int B, int T, int k, int32_t* topk_idx,
+                               float* gates, const PermuteOut& o, hipStream_t s) {
+  if (T > kChunkTokens) return hipErrorInvalidValue;
+  const bool wide = lanes_per_token(T, o.E) == 16;
+  return quad_form(o.E, k, [&](auto epl, auto km) {
+    constexpr int EPL = decltype(epl)::value, KM = decltype(km)::value;
+    if (wide)
+      hipLaunchKernelGGL((k_route_block_batch<16, EPL, KM>), dim3(B), dim3(kPermThreads), 0, s,
+                         logits, T, k, topk_idx, gates, o);
+    else
+      hipLaunchKernelGGL((k_route_block_batch<4, 4 * EPL, KM>), dim3(B), dim3(kPermThreads), 0, s,
+                         logits, T, k, topk_idx, gates, o);
+  });
+}
+
 hipError_t launch_permute(const int32_t* topk_idx, int T, int k, int32_t* bad_flag,
                           const PermuteOut& o, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s) {
   hipExtLaunchKernelGGL(k_permute, dim3(1), dim3(kPermThreads), 0, s, ev0, ev1, 0, topk_idx, T, k,
@@ -1970,12 +2080,20 @@ hipError_t launch_permute_batch(const int32_t* topk_idx, int B, int T, int k,
 hipError_t launch_route_fused(const float* logits, int T, int k, int32_t* topk_idx, float* gates,
                               int32_t* sync, const PermuteOut& o, hipEvent_t ev0, hipEvent_t ev1,
                               hipStream_t s) {
-  const bool solo = route_solo(T, k);
+  const bool solo = solo_block(T, o.E);
+  const bool wide = lanes_per_token(T, o.E) == 16;
   return quad_form(o.E, k, [&](auto epl, auto km) {
     constexpr int EPL = decltype(epl)::value, KM = decltype(km)::value;
+    if constexpr (EPL == 4) {   // 4 lanes a token: up to 64 experts alone
+      if (solo && !wide) {
+        hipExtLaunchKernelGGL((k_route_solo<4, 4 * EPL, KM>), dim3(1), dim3(kPermThreads), 0, s,
+                              ev0, ev1, 0, logits, T, k, topk_idx, gates, o);
+        return;
+      }
+    }
     if (solo)
-      hipExtLaunchKernelGGL(k_route_solo<EPL, KM>, dim3(1), dim3(kPermThreads), 0, s, ev0, ev1, 0,
-                            logits, T, k, topk_idx, gates, o);
+      hipExtLaunchKernelGGL((k_route_solo<16, EPL, KM>), dim3(1), dim3(kPermThreads), 0, s, ev0,
+                            ev1, 0, logits, T, k, topk_idx, gates, o);
     else
       hipExtLaunchKernelGGL(k_route_fused<EPL, KM>, dim3((T + 15) / 16), dim3(256), 0, s, ev0, ev1,
                             0, logits, T, k, topk_idx, gates, sync, o);
@@ -2072,8 +2190,11 @@ extern "C" oled_status oled_route_noalloc(const float* logits_dev, int32_t T, in
   o.bad_out = nonfinite_dev;   // written by the planning workgroup (cv.hdr null: no cache)
 
   // the counters and flags start at zero (the launches also leave them zero);
-  // the smallest blocks use none
-  if (!oled::route_solo(T, k)) {
+  // a block that one workgroup takes uses none. One launch against two or three:
+  // 96 x 64 7 against 12.5 us, 256 x 64 9.0 against 11.4, 256 x 128 12.4 against 12.8,
+  // 384 x 128 16.0 against 14.1, 130 x 256 (k = 16) 19.5 against 13.6.
+  const bool block = T <= 64 || (T <= 256 && E <= 128 && k <= 8);
+  if (!block) {
     hipLaunchKernelGGL(k_clear_head, dim3(1), dim3(kScratchHead), 0, s, sc);
     if (hipGetLastError() != hipSuccess) {
       oled::set_noctx_error("oled_route_noalloc: launch failed");
@@ -2081,7 +2202,9 @@ extern "C" oled_status oled_route_noalloc(const float* logits_dev, int32_t T, in
     }
   }
   hipError_t e;
-  if (oled::route_fused(T, k)) {
+  if (block) {
+    e = oled::launch_route_blocks(logits_dev, 1, T, k, topk_idx_dev, gates_dev, o, s);
+  } else if (oled::route_fused(T, k)) {
     e = oled::launch_route_fused(logits_dev, T, k, topk_idx_dev, gates_dev, sc + 2, o, nullptr,
                                  nullptr, s);
   } else {
@@ -2111,6 +2234,17 @@ namespace {
 __global__ __launch_bounds__(256) void k_clear_ints(int32_t* p, int n) {
   const int i = blockIdx.x * 256 + static_cast<int>(threadIdx.x);
   if (i < n) p[i] = 0;
+}
+
+// Whether a workgroup takes a whole block of the batch: while its instruction
+// stream (tokens x experts, twice that for the longer lists above k = 8) is
+// shorter than the launches it saves. One launch against five: 16 blocks of 512 x
+// 64, k = 8, 16.2 against 18.5 us, 257 x 128 14.1 against 19.3, 512 x 128 22.5 against
+// 19.6, 257 x 256, k = 16, 32.0 against 30.8; 512 blocks of 512 x 64 36.8 against 42.1,
+// of 512 x 128 53.6 against 52.0. Up to two blocks a compute unit were measured.
+constexpr int kBlockBatchMax = 512;
+bool whole_blocks(int B, int T, int E, int k) {
+  return B <= kBlockBatchMax && T <= oled::kChunkTokens && T * E * (k > 8 ? 2 : 1) <= 36864;
 }
 
 size_t batch_head_ints(int32_t B) { return ((2 * static_cast<size_t>(B) + 63) / 64) * 64; }
@@ -2150,25 +2284,28 @@ extern "C" oled_status oled_route_batch(const float* logits_dev, int32_t B, int3
     return OLED_ERR_INVALID_ARG;
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  int32_t* ws = static_cast<int32_t*>(workspace_dev);
-  int32_t* bad = ws;                                  // [B] non-finite flags of the top-k launch
-  int32_t* chunk_base = ws + batch_head_ints(B);      // [B][chunks][E]
-  const int n_head = B;
-  hipLaunchKernelGGL(k_clear_ints, dim3((n_head + 255) / 256), dim3(256), 0, s, ws, n_head);
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess)
-    e = oled::launch_route_topk(logits_dev, B * T, E, k, topk_idx_dev, gates_dev, bad, nullptr,
-                                nullptr, s, T);
-  if (e == hipSuccess) {
-    oled::PermuteOut o{};
-    o.counts = counts_dev;
-    o.offsets = offsets_dev;
-    o.perm = perm_dev;
-    o.inv_perm = inv_perm_dev;
-    o.gates = gates_dev;
-    o.E = E;
-    o.bad_out = nonfinite_dev;
-    e = oled::launch_permute_batch(topk_idx_dev, B, T, k, bad, chunk_base, o, s);
+  oled::PermuteOut o{};
+  o.counts = counts_dev;
+  o.offsets = offsets_dev;
+  o.perm = perm_dev;
+  o.inv_perm = inv_perm_dev;
+  o.gates = gates_dev;
+  o.E = E;
+  o.bad_out = nonfinite_dev;
+  hipError_t e;
+  if (whole_blocks(B, T, E, k)) {
+    e = oled::launch_route_blocks(logits_dev, B, T, k, topk_idx_dev, gates_dev, o, s);
+  } else {
+    int32_t* ws = static_cast<int32_t*>(workspace_dev);
+    int32_t* bad = ws;                                  // [B] non-finite flags of the top-k launch
+    int32_t* chunk_base = ws + batch_head_ints(B);      // [B][chunks][E]
+    hipLaunchKernelGGL(k_clear_ints, dim3((B + 255) / 256), dim3(256), 0, s, ws, B);
+    e = hipGetLastError();
+    if (e == hipSuccess)
+      e = oled::launch_route_topk(logits_dev, B * T, E, k, topk_idx_dev, gates_dev, bad, nullptr,
+                                  nullptr, s, T);
+    if (e == hipSuccess)
+      e = oled::launch_permute_batch(topk_idx_dev, B, T, k, bad, chunk_base, o, s);
   }
   if (e != hipSuccess) {
     oled::set_noctx_error("oled_route_batch: launch failed");

@@ -81,7 +81,7 @@ def test_nonfinite_rows_rank_by_key(E):
 
 
 @pytest.mark.parametrize("E,k", [(8, 2), (60, 6), (64, 8), (128, 8), (128, 16), (256, 4), (256, 16)])
-@pytest.mark.parametrize("T", [1, 15, 16, 17, 31, 32, 33, 48, 63, 64, 65])
+@pytest.mark.parametrize("T", [1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 256, 257])
 def test_smallest_blocks(E, k, T):
     _check(_logits(T, E, T, True), E, k, 1, False)
 
@@ -90,3 +90,15 @@ def test_smallest_blocks(E, k, T):
 @pytest.mark.parametrize("E,k", [(32, 2), (64, 8), (200, 3), (256, 16)])
 def test_around_the_bounds_of_the_forms(E, k, T):
     _check(_logits(T, E, T, True), E, k, 1, False)
+
+
+@pytest.mark.parametrize("E,k", [(8, 2), (60, 6), (64, 8), (128, 1), (128, 16), (256, 16)])
+@pytest.mark.parametrize("B,T", [(1, 512), (3, 511), (2, 513), (7, 257), (3, 72), (3, 73), (9, 33), (512, 5),
+                                 (513, 5), (40, 1)])
+def test_batches_of_one_chunk(E, k, B, T):
+    lg = _logits(B * T, E, T + B, True)
+    if B == 7:
+        lg[3 * T + 5, E // 2] = np.nan
+    _check(lg, E, k, B, True)
+    if B == 1:
+        _check(lg, E, k, B, False)
