@@ -36,6 +36,69 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
   return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), 63));
 }
 
+__device__ __forceinline__ double readlane_f64(double x, int lane) {
+  const uint64_t b = __double_as_longlong(x);
+  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(b)), lane);
+  const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(b >> 32)), lane);
+  return __longlong_as_double(static_cast<long long>((static_cast<uint64_t>(hi) << 32) | lo));
+}
+
+// Routes one token with one wavefront; lane l owns experts l, l+64, ... (EPL
+// per lane) of the logit row (global memory or LDS). Slot j takes the largest
+// remaining key in the order (logit desc, id asc): a wavefront maximum of the
+// ordered keys, then the lowest expert id holding it (ballots in expert
+// order), which leaves the candidates. Keys of valid experts are >= 1, so a
+// taken or absent expert (key 0) is never chosen again. Lane j < k keeps slot
+// j's expert and logit, takes e_j = exp(l_j - l_0) in fp64; every lane sums
+// e_0 + ... + e_{k-1} in slot order, and lane j returns g_j = fl32(e_j / s)
+// and its expert (else -1). *bad is set if a logit is non-finite.
+template <int EPL>
+__device__ __forceinline__ int route_token(const float* row, int E, int k,
+                                           float* __restrict__ gate_out, int* bad) {
+  const int lane = threadIdx.x & 63;
+  uint32_t ok[EPL];
+  int nonfinite = 0;
+#pragma unroll
+  for (int q = 0; q < EPL; ++q) {
+    const int e = lane + 64 * q;
+    ok[q] = 0u;
+    if (e < E) {
+      const float v = row[e];
+      nonfinite |= !__builtin_isfinite(v);
+      ok[q] = max(ord_key(v), 1u);
+    }
+  }
+  *bad |= __any(nonfinite);
+  int my_e = -1;
+  uint32_t my_key = 0u, key0 = 0u;
+  for (int j = 0; j < k; ++j) {
+    uint32_t lm = ok[0];
+#pragma unroll
+    for (int q = 1; q < EPL; ++q) lm = max(lm, ok[q]);
+    const uint32_t m = wave_max(lm);
+    int id = -1;
+#pragma unroll
+    for (int q = 0; q < EPL; ++q) {
+      const uint64_t b = __ballot(ok[q] == m);
+      if (id < 0 && b != 0ull) id = 64 * q + __builtin_ctzll(b);
+    }
+#pragma unroll
+    for (int q = 0; q < EPL; ++q)
+      if (lane + 64 * q == id) ok[q] = 0u;
+    if (lane == j) {
+      my_e = id;
+      my_key = m;
+    }
+    if (j == 0) key0 = m;
+  }
+  const double v0 = static_cast<double>(ord_value(key0));
+  const double ex = lane < k ? exp(static_cast<double>(ord_value(my_key)) - v0) : 0.0;
+  double s = 0.0;
+  for (int j = 0; j < k; ++j) s += readlane_f64(ex, j);
+  *gate_out = static_cast<float>(ex / s);
+  return lane < k ? my_e : -1;
+}
+
 // Inclusive prefix sum over the 64 lanes of a wavefront: shifts by 1, 2, 4
 // and 8 within each row of 16 lanes, then the row totals carried to the rows
 // above (DPP row_shr and row_bcast; lanes without a source add zero).
@@ -59,6 +122,27 @@ __device__ __forceinline__ int row16_incl_scan(int v) {
   v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
   v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
   return v;
+}
+
+// Mid-sized blocks, one token per wavefront. T tokens in blocks of Tb: a
+// non-finite logit of token t sets bad_flag[t / Tb].
+template <int EPL>
+__global__ __launch_bounds__(256) void k_route_wave(const float* __restrict__ logits, int T, int E,
+                                                    int k, int32_t* __restrict__ topk_idx,
+                                                    float* __restrict__ gates,
+                                                    int32_t* __restrict__ bad_flag, int Tb) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int nwaves = gridDim.x * 4;
+  for (int t = blockIdx.x * 4 + wave; t < T; t += nwaves) {
+    float g;
+    int bad = 0;
+    const int e = route_token<EPL>(logits + static_cast<size_t>(t) * E, E, k, &g, &bad);
+    if (lane < k) {
+      topk_idx[static_cast<size_t>(t) * k + lane] = e;
+      gates[static_cast<size_t>(t) * k + lane] = g;
+    }
+    if (bad && lane == 0) atomicOr(&bad_flag[t / Tb], 1);
+  }
 }
 
 // Large blocks: one token per lane. A wavefront takes 64 tokens; their
@@ -539,7 +623,7 @@ __device__ __forceinline__ bool route_group(const float* logits, int t, int T, i
   return bad;
 }
 
-// T tokens in blocks of Tb: a non-finite logit of token t sets bad_flag[t / Tb].
+// As k_route_wave, with four tokens a wavefront.
 template <int EPL, int KM>
 __global__ __launch_bounds__(256) void k_route_topk(const float* __restrict__ logits, int T, int E,
                                                     int k, int32_t* __restrict__ topk_idx,
@@ -569,7 +653,9 @@ __global__ __launch_bounds__(256) void k_route_topk(const float* __restrict__ lo
 // L2: twice the bytes of the logits, which bounded the launch. The gates are
 // computed when 64 tokens are ranked, one token per lane.
 // Measured at 32 blocks of 65535 tokens x 128 experts, k = 8: 342 ->
-// 279 us (the whole call with the permutation and priority sums 416 -> 354).
+// 280 us (the whole call with the permutation and priority sums 416 -> 354), the
+// logits fetched once; vector instructions then fill 0.61 of the cycles. Freeing
+// the buffer before the ranking, for twice the bytes in flight, changed nothing.
 template <int KP, int KM, int G>
 __global__ __launch_bounds__(256) void k_route_rows(const float* __restrict__ logits, int T, int k,
                                                     int32_t* __restrict__ topk_idx,
@@ -717,6 +803,12 @@ constexpr bool solo_block(int T, int E) { return T <= 64 || (E <= 64 && T <= 128
 // 21.5, 22.2 and 24.7 us, in these forms 23.8, 27.5 and 28.4; of 8192 and 16384 x 8
 // (k = 2) 20.2 and 22.1 against 20.9 and 21.1.
 constexpr int lane_tokens_min(int E) { return E > 32 ? 16384 : 8192; }
+// Up to here one token per wavefront: three times the instructions of four a
+// wavefront, but a shorter program on four times the wavefronts. Routing and
+// permutation (k = 8) of 279 x 64, 1000 x 64, 3001 x 64 and 2048 x 256 10.9, 16.7, 20.3 and
+// 21.3 us against 11.3, 17.3, 21.5 and 21.9; of 8192 x 64, x 128 and x 256 22.3, 23.4 and
+// 25.6 against 22.1, 22.2 and 23.9.
+constexpr int kWaveTokensMax = 4096;
 constexpr int kRouteStreamGrid = 512;       // DMA-streamed top-k: two workgroups per CU
 constexpr int kGateFullGrid = 256;          // gate GEMM workgroups that fill the compute units
 constexpr int kChunkedMinTokens = 1024;     // and permute over many workgroups
@@ -2001,6 +2093,19 @@ hipError_t launch_route_topk(const float* logits, int T, int E, int k, int32_t* 
     else if (k <= 4) go(integral_constant<int, 5>{}, integral_constant<int, 4>{});
     else if (k <= 8) go(integral_constant<int, 9>{}, integral_constant<int, 8>{});
     else go(integral_constant<int, 17>{}, integral_constant<int, 16>{});
+    return hipGetLastError();
+  }
+  if (T <= kWaveTokensMax) {
+    const dim3 grid((T + 3) / 4);
+    if (E <= 64)
+      hipExtLaunchKernelGGL(k_route_wave<1>, grid, dim3(256), 0, s, ev0, ev1, 0, logits, T, E, k,
+                            topk_idx, gates, bad_flag, Tb);
+    else if (E <= 128)
+      hipExtLaunchKernelGGL(k_route_wave<2>, grid, dim3(256), 0, s, ev0, ev1, 0, logits, T, E, k,
+                            topk_idx, gates, bad_flag, Tb);
+    else
+      hipExtLaunchKernelGGL(k_route_wave<4>, grid, dim3(256), 0, s, ev0, ev1, 0, logits, T, E, k,
+                            topk_idx, gates, bad_flag, Tb);
     return hipGetLastError();
   }
   const int blocks = (T + 15) / 16;

@@ -86,7 +86,7 @@ def test_smallest_blocks(E, k, T):
     _check(_logits(T, E, T, True), E, k, 1, False)
 
 
-@pytest.mark.parametrize("T", [1024, 1025, 8192, 8193, 16384, 16385])
+@pytest.mark.parametrize("T", [1024, 1025, 4096, 4097, 8192, 8193, 16384, 16385])
 @pytest.mark.parametrize("E,k", [(32, 2), (64, 8), (200, 3), (256, 16)])
 def test_around_the_bounds_of_the_forms(E, k, T):
     _check(_logits(T, E, T, True), E, k, 1, False)
