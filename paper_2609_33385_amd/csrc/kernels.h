@@ -239,9 +239,10 @@ hipError_t launch_permute_batch(const int32_t* topk_idx, int B, int T, int k,
                                 const int32_t* bad_flag, int32_t* chunk_base, const PermuteOut& o,
                                 hipStream_t s);
 
-// K1+K2 as one launch for blocks with T*k <= 1024 (route_fused true): the
-// last workgroup to finish routing permutes. sync: 2 device ints, zero
-// before the first launch; the kernel leaves them zero.
+// K1+K2 as one launch for blocks with T*k <= 1024 (route_fused true): one
+// workgroup takes the smallest, else the last workgroup to finish routing
+// permutes. sync: 2 device ints, zero before the first launch; the kernel
+// leaves them zero.
 bool route_fused(int T, int k);
 hipError_t launch_route_fused(const float* logits, int T, int k, int32_t* topk_idx, float* gates,
                               int32_t* sync, const PermuteOut& o, hipEvent_t ev0, hipEvent_t ev1,
