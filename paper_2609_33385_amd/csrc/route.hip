@@ -165,32 +165,35 @@ constexpr int kLaneChunk = 32;
 constexpr int kLaneRow = kLaneChunk + 1;   // padded LDS row (floats): conflict-free lane reads
 constexpr int kLaneRowsPerLoad = 64 / kLaneChunk;
 
-// The whole wavefront ranks one row with full keys (E <= 256): k rounds of a
+// The whole wavefront ranks one row with full keys (E <= 64 Q): k rounds of a
 // wavefront maximum, the lowest id holding it taken by ballot (keys of valid
 // experts are >= 1, a taken or absent expert's is 0); the lanes that own the
 // token keep the ids.
-template <int KM>
+template <int KM, int Q = kMaxExperts / 64>
 __device__ __forceinline__ void wave_topk_ids(const float* row, int E, int k, bool mine,
                                               int32_t (&ids)[KM]) {
   const int lane = threadIdx.x & 63;
-  uint32_t ok[4];
+  uint32_t ok[Q];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
+  for (int q = 0; q < Q; ++q) {
     const int e = lane + 64 * q;
     ok[q] = e < E ? max(ord_key(row[e]), 1u) : 0u;
   }
 #pragma unroll
   for (int j = 0; j < KM; ++j) {
     if (j < k) {
-      const uint32_t m = wave_max(max(max(ok[0], ok[1]), max(ok[2], ok[3])));
+      uint32_t lm = ok[0];
+#pragma unroll
+      for (int q = 1; q < Q; ++q) lm = max(lm, ok[q]);
+      const uint32_t m = wave_max(lm);
       int id = -1;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int q = 0; q < Q; ++q) {
         const uint64_t bq = __ballot(ok[q] == m);
         if (id < 0 && bq != 0ull) id = 64 * q + __builtin_ctzll(bq);
       }
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
+      for (int q = 0; q < Q; ++q)
         if (lane + 64 * q == id) ok[q] = 0u;
       if (mine) ids[j] = id;
     }
@@ -528,6 +531,141 @@ __device__ __forceinline__ void merge_pair(float (&key)[KP]) {
       if (((i - 1) & d) == 0) exchange(i, i + d);
 }
 
+// As dpp_pair, of doubles.
+template <int STEP>
+__device__ __forceinline__ double dpp_pair64(double v) {
+  constexpr int kCtrl = STEP == 0 ? 0xB1 : STEP == 1 ? 0x4E : STEP == 2 ? 0x141 : 0x140;
+  const uint64_t b = static_cast<uint64_t>(__double_as_longlong(v));
+  const int lo = static_cast<int>(static_cast<uint32_t>(b));
+  const int hi = static_cast<int>(static_cast<uint32_t>(b >> 32));
+  const uint32_t plo = __builtin_amdgcn_update_dpp(lo, lo, kCtrl, 0xf, 0xf, false);
+  const uint32_t phi = __builtin_amdgcn_update_dpp(hi, hi, kCtrl, 0xf, 0xf, false);
+  return __longlong_as_double(static_cast<long long>((static_cast<uint64_t>(phi) << 32) | plo));
+}
+
+// The whole order of a logit and its expert as one number: 2^52 + 256 * ordered
+// key + 255 - id, so that a maximum and a minimum order (logit desc, id asc), of
+// non-finite logits too. 0 stands for an absent expert.
+__device__ __forceinline__ double exact_key(float x, int rid) {
+  const uint32_t o = max(ord_key(x), 1u);
+  return __longlong_as_double(static_cast<long long>(
+      (static_cast<uint64_t>(0x43300000u | (o >> 24)) << 32) | ((o << 8) | static_cast<uint32_t>(rid))));
+}
+
+// Sorts v in descending order (SORT: any v; else v falls and then rises), N a
+// power of two.
+template <bool SORT, int N>
+__device__ __forceinline__ void bitonic(double* v) {
+#pragma unroll
+  for (int w = SORT ? 2 : N; w <= N; w <<= 1)
+#pragma unroll
+    for (int d = w / 2; d >= 1; d >>= 1)
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+        if ((i & d) == 0) {
+          const double hi = fmax(v[i], v[i + d]), lo = fmin(v[i], v[i + d]);
+          v[i] = (i & w) == 0 || w == N ? hi : lo;
+          v[i + d] = (i & w) == 0 || w == N ? lo : hi;
+        }
+}
+
+// The KM largest exact keys of each token, by the lanes of the token as in
+// route_group, for all tokens of the wavefront at once; 255 - their ids in order. G
+// experts of a lane at a time are sorted and merged into its list, with half the
+// operations of an insertion each.
+template <int LPT, int EPL, int KM>
+__device__ __forceinline__ void exact_ids(int l, int E, const float* src, int32_t (&rid)[KM]) {
+  constexpr int G = EPL < KM ? EPL : KM;
+  double key[KM], b[KM];
+#pragma unroll
+  for (int j = 0; j < KM; ++j) key[j] = 0.0;
+  auto merge = [&]() {   // the KM largest of key and b, both descending
+#pragma unroll
+    for (int j = 0; j < KM; ++j) key[j] = fmax(key[j], b[KM - 1 - j]);
+    bitonic<false, KM>(key);
+  };
+#pragma unroll 1
+  for (int i0 = 0; i0 < EPL && LPT * i0 < E; i0 += G) {
+    float x[G];
+#pragma unroll
+    for (int i = 0; i < G; ++i) x[i] = src[min(l + LPT * (i0 + i), E - 1)];
+#pragma unroll
+    for (int i = 0; i < KM; ++i) {
+      const int e = l + LPT * (i0 + i);
+      b[i] = i < G && e < E ? exact_key(x[i < G ? i : 0], 255 - e) : 0.0;
+    }
+    bitonic<true, G>(b);
+    merge();
+  }
+  auto step = [&](auto dpp) {
+#pragma unroll
+    for (int j = 0; j < KM; ++j) b[j] = dpp_pair64<decltype(dpp)::value>(key[j]);
+    merge();
+  };
+  step(std::integral_constant<int, 0>{});
+  step(std::integral_constant<int, 1>{});
+  if constexpr (LPT == 16) {
+    step(std::integral_constant<int, 2>{});
+    step(std::integral_constant<int, 3>{});
+  }
+#pragma unroll
+  for (int j = 0; j < KM; ++j) rid[j] = static_cast<int>(__double_as_longlong(key[j]) & 0xFF);
+}
+
+// Whether the tied tokens of a wavefront (a bit each) are ranked one after the
+// other: about 0.2 us a route, against 1, 1.2 and 1.8 us for all of them at once
+// with 4, 8 and 16 experts a lane of 16, and 1.8, 3 and 6 with 16, 32 and 64 of 4.
+template <int LPT, int EPL>
+__device__ __forceinline__ bool few_tied(uint64_t todo, int k) {
+  return __popcll(todo) * k <= (LPT == 4 ? EPL / 2 : 4 + EPL / 4);
+}
+
+template <int KM>
+struct Rids {
+  int32_t v[KM];   // 255 - id, or -1: as before
+};
+
+// Ranks the tokens of route_group with `tied` set (and maybe others of the
+// wavefront, with the same result) by their logits in full: few of them one after
+// the other, else rows of one value (padding) at sight and the rest by exact_ids.
+// Not inlined: in line it cost the blocks without a tie 0.2 to 0.5 us.
+template <int LPT, int EPL, int KM>
+__device__ __noinline__ Rids<KM> rank_tied(const float* logits, int T, int E, int k, int t,
+                                           bool tied) {
+  const int lane = threadIdx.x & 63, l = lane % LPT, row = lane / LPT;
+  const float* src = logits + static_cast<size_t>(min(t, T - 1)) * E;
+  Rids<KM> r;
+#pragma unroll
+  for (int j = 0; j < KM; ++j) r.v[j] = -1;
+  uint64_t todo = __ballot(tied && t < T && l == 0);
+  if (!few_tied<LPT, EPL>(todo, k)) {
+    const float x0 = src[0];
+    bool other = false;
+#pragma unroll 16
+    for (int i = 0; i < EPL; ++i) other |= src[min(l + LPT * i, E - 1)] != x0;
+    if (((__ballot(other) >> (LPT * row)) & ((1ull << LPT) - 1)) == 0ull) {
+      tied = false;   // a row of one value: ids 0, 1, ...
+#pragma unroll
+      for (int j = 0; j < KM; ++j) r.v[j] = 255 - j;
+    }
+    todo = __ballot(tied && t < T && l == 0);
+    if (!few_tied<LPT, EPL>(todo, k)) {
+      exact_ids<LPT, EPL, KM>(l, E, src, r.v);
+      return r;
+    }
+  }
+  for (; todo != 0ull; todo &= todo - 1) {
+    const int owner = __builtin_ctzll(todo);
+    const bool own = row == owner / LPT;
+    wave_topk_ids<KM, (LPT * EPL + 63) / 64>(
+        logits + static_cast<size_t>(__builtin_amdgcn_readlane(t, owner)) * E, E, k, own, r.v);
+    if (own)
+#pragma unroll
+      for (int j = 0; j < KM; ++j) r.v[j] = 255 - r.v[j];
+  }
+  return r;
+}
+
 // Small and mid-sized blocks: a wavefront ranks 64 / LPT tokens, LPT lanes each.
 // Lane l of a row takes experts l, l + LPT, ... (at most EPL) into a descending
 // list of packed keys, and the LPT lists are merged. Lane l then hands on routes
@@ -535,11 +673,19 @@ __device__ __forceinline__ void merge_pair(float (&key)[KP]) {
 // exp(l_j - l_0) in fp64, s = e_0 + ... + e_{k-1} in slot order (the exponentials
 // meet in s_ex, the wavefront's own). With 16 lanes the logits pass through s_val,
 // also the wavefront's own, where the routes' exact logits are read back by id;
-// with fewer they are read from memory again, just behind the first time. Ties of
-// class and non-finite logits as above. Returns whether the row has a non-finite
-// logit. What bounds these calls is the length of the instruction stream: one
-// token a wavefront, with a wavefront maximum per route, issued three times as
-// many instructions a token as 16 lanes, and 16 lanes three times as many as 4.
+// with fewer they are read from memory again, just behind the first time. Returns
+// whether the row has a non-finite logit. What bounds these calls is the length of
+// the instruction stream: one token a wavefront, with a wavefront maximum per
+// route, issued three times as many instructions a token as 16 lanes, and 16 lanes
+// three times as many as 4.
+// Ties: the keys hold 255 - id, so where no logit of the wavefront has a bit below
+// its top 24 (logits rounded to 16 bits, small whole numbers), equal positive
+// logits are in order already. Else, where two of the k + 1 best of a token share a
+// class, or a logit is not finite, rank_tied ranks the tied tokens again in full.
+// One block of 128 tokens x 64 experts (k = 8) without a cache: 6.5 us, 7.0 with
+// logits rounded to bf16, 7.6 with equal logits, 10.4 with logits of two values; with
+// every tied token ranked by the whole wavefront 6.6, 13.0, 33 and 33. 64 x 256: 8.2,
+// 9.2, 9.9 and 15.1 against 8.7, 13.2, 18.9 and 19.0.
 template <int LPT, int EPL, int KM, class F>
 __device__ __forceinline__ bool route_group(const float* logits, int t, int T, int E, int k,
                                             float* s_val, double* s_ex, F emit) {
@@ -552,6 +698,7 @@ __device__ __forceinline__ bool route_group(const float* logits, int t, int T, i
   float* val = LPT == 16 ? s_val + row * W : nullptr;
   float key[KP];
   float zeros = 0.f;   // sum of 0 * logit: not a number once a logit is non-finite
+  uint32_t low = 0u;   // bits set in any logit
 #pragma unroll
   for (int j = 0; j < KP; ++j) key[j] = -__builtin_inff();
   constexpr int EB = EPL < 16 ? EPL : 16;   // loads in flight
@@ -566,7 +713,8 @@ __device__ __forceinline__ bool route_group(const float* logits, int t, int T, i
       const int e = l + LPT * (i0 + i);
       if constexpr (LPT == 16) val[e] = x[i];
       zeros = __builtin_fmaf(x[i], 0.f, zeros);
-      insert_packed<KP>(key, e < E ? packed_key(x[i], e) : -__builtin_inff());
+      low |= __float_as_uint(x[i]);
+      insert_packed<KP>(key, e < E ? packed_key(x[i], 255 - e) : -__builtin_inff());
     }
   }
   merge_pair<KP, 0>(key);
@@ -584,28 +732,39 @@ __device__ __forceinline__ bool route_group(const float* logits, int t, int T, i
 #pragma unroll
   for (int j = 0; j + 1 < KP; ++j)
     if (j < k) amb |= same_class(key[j], key[j + 1]);
-  int32_t id[KM];
+  int32_t rid[KM];   // 255 - id
 #pragma unroll
-  for (int j = 0; j < KM; ++j) id[j] = static_cast<int>(__float_as_uint(key[j]) & 0xFFu);
-  for (uint64_t todo = __ballot(amb && t < T && l == 0); todo != 0ull; todo &= todo - 1) {
-    const int owner = __builtin_ctzll(todo);
-    wave_topk_ids<KM>(logits + static_cast<size_t>(__builtin_amdgcn_readlane(t, owner)) * E, E, k,
-                      row == owner / LPT, id);
+  for (int j = 0; j < KM; ++j) rid[j] = static_cast<int>(__float_as_uint(key[j]) & 0xFFu);
+  if (__builtin_expect(__any(amb), 0)) {
+    if (!__any((low & 0xFFu) != 0u)) {   // only ties of negative logits and of zeros are left
+      amb = bad;
+#pragma unroll
+      for (int j = 0; j + 1 < KP; ++j)
+        if (j < k) amb |= same_class(key[j], key[j + 1]) && !(key[j + 1] >= 0x1p-126f);
+    }
+    if (__any(amb)) {
+      const Rids<KM> r = rank_tied<LPT, EPL, KM>(logits, T, E, k, t, amb);
+      if (r.v[0] >= 0) {
+#pragma unroll
+        for (int j = 0; j < KM; ++j) rid[j] = r.v[j];
+      }
+    }
   }
   int mine[M];
 #pragma unroll
   for (int m = 0; m < M; ++m) {
-    mine[m] = id[LPT * m < KM ? LPT * m : 0];
+    mine[m] = rid[LPT * m < KM ? LPT * m : 0];
 #pragma unroll
     for (int p = 1; p < LPT; ++p)
-      if (LPT * m + p < KM && l == p) mine[m] = id[LPT * m + p];
+      if (LPT * m + p < KM && l == p) mine[m] = rid[LPT * m + p];
+    mine[m] = 255 - mine[m];
   }
   if constexpr (LPT == 16) wave_lds_fence();
-  auto logit = [&](int e) {   // ids past k are those of absent experts, 0
+  auto logit = [&](int e) {   // ids past k may be those of absent experts
     if constexpr (LPT == 16) return static_cast<double>(val[e & (W - 1)]);
     else return static_cast<double>(src[min(e, E - 1)]);
   };
-  const double v0 = logit(id[0]);
+  const double v0 = logit(255 - rid[0]);
   double* sx = s_ex + row * KM;
   double ex[M];
 #pragma unroll
