@@ -2454,10 +2454,11 @@ extern "C" oled_status oled_route_noalloc(const float* logits_dev, int32_t T, in
   o.bad_out = nonfinite_dev;   // written by the planning workgroup (cv.hdr null: no cache)
 
   // the counters and flags start at zero (the launches also leave them zero);
-  // a block that one workgroup takes uses none. One launch against two or three:
-  // 96 x 64 7 against 12.5 us, 256 x 64 9.0 against 11.4, 256 x 128 12.4 against 12.8,
-  // 384 x 128 16.0 against 14.1, 130 x 256 (k = 16) 19.5 against 13.6.
-  const bool block = T <= 64 || (T <= 256 && E <= 128 && k <= 8);
+  // a block that one workgroup takes uses none. One launch against two or three, in
+  // replayed graphs: 96 x 64 6.3 against 12.3 us, 256 x 64 8.7 against 10.4, 128 x 128
+  // 8.4 against 14.4, 192 x 128 (three wavefronts a SIMD) 10.1 against 10.6, but 208 x
+  // 96 and x 128 11.2 and 11.7 against 10.5 and 10.9.
+  const bool block = T <= 64 || (T <= (E <= 64 ? 256 : 192) && E <= 128 && k <= 8);
   if (!block) {
     hipLaunchKernelGGL(k_clear_head, dim3(1), dim3(kScratchHead), 0, s, sc);
     if (hipGetLastError() != hipSuccess) {

@@ -54,7 +54,7 @@ def test_order_of_ties(kind, T, E, k):
         _check(np.concatenate([lg, lg[::-1], np.full_like(lg, -1.5)]), E, k, 3, True)
 
 
-def _replayed_us(lg, k, n=50):
+def replayed_us(lg, k, n=50):
     """Time of one routing call among n in a replayed graph, the least of 8 replays."""
     from paper_2609_33385_amd import oled
     T, E = lg.shape
@@ -87,8 +87,8 @@ def test_ties_cost_one_more_ranking(T, E, k):
     longer: 1.1 to 1.9 of the untied time is measured, 2.3 to 5.4 where the tied
     tokens of a wavefront are ranked one after the other."""
     rng = np.random.default_rng(T)
-    plain = _replayed_us((3 * rng.standard_normal((T, E))).astype(np.float32), k)
+    plain = replayed_us((3 * rng.standard_normal((T, E))).astype(np.float32), k)
     for kind in ("bf16", "one-value", "two-values"):
-        tied = _replayed_us(_logits(kind, T, E), k)
+        tied = replayed_us(_logits(kind, T, E), k)
         print(f"[ties] {T}x{E} k={k} {kind}: {tied:.2f} us, untied {plain:.2f}", flush=True)
         assert tied <= 2.1 * plain, f"{kind}: {tied:.2f} us against {plain:.2f}"
