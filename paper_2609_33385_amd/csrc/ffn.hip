@@ -755,7 +755,7 @@ __device__ __forceinline__ void dense_block(const FfnLaunch& a, int b, u32x4_t (
   const int rows_exp = __builtin_amdgcn_readlane(mine.z, g & 63);
   const int hslot = __builtin_amdgcn_readlane(mine.w, g & 63);
   const int rows = rows_exp & 0xFFFF, expert = (rows_exp >> 16) & (kMaxExperts - 1);
-  const int m = dense_items(rows, RR), per = dense_item_rows(rows, RR);
+  const int m = dense_items(rows, RR);
   const int ng = (m + kDenseGroup - 1) / kDenseGroup, gs = (m + ng - 1) / ng;
   int rem = t - first * nf;
   const int sub = rem / (gs * nf);
@@ -763,10 +763,11 @@ __device__ __forceinline__ void dense_block(const FfnLaunch& a, int b, u32x4_t (
   const int gi = min(gs, m - sub * gs);
   if (gi <= 0) return;
   const int ft = rem / gi, i = sub * gs + rem - ft * gi;
+  const DenseItem part = dense_item(rows, RR, i);
   WorkItem it;
   it.expert = expert;
-  it.row_begin = row0 + i * per;
-  it.rows = min(per, rows - i * per);
+  it.row_begin = row0 + part.first;
+  it.rows = part.rows;
   it.pad = hslot;
   const int slot = it.pad >= 0 ? it.pad : a.slot_of[it.expert];
   if (slot < 0 || slot >= a.n_slots || it.rows <= 0 || it.rows > RR || ft >= nf) return;
