@@ -1245,6 +1245,13 @@ __device__ __forceinline__ void permute_body(const int32_t* idx, int T, int k, i
   }
   __syncthreads();
 
+  // Large tiles of few experts: every XCD an equal number instead of an equal cost.
+  // Their tiles cost nearly the same, and a launch holds few rounds of them (one tile
+  // a compute unit): a range a tile longer than the others is a round more. Layers of
+  // 10000 tokens x 8 experts (k = 4) 538 -> 511 us, of 11739 x 8 (Zipf) 611 -> 588, of
+  // 10000 x 16 (k = 8) 979 -> 959; x 32 within 2% either way, but 12000 x 128 (Zipf)
+  // 1233 -> 1274.
+  const bool even = o.dense_shift == 8 && s_stat[10] <= 16;
   for (int e = tid; e < E; e += nthr) {
     const int c = s_cnt[e];
     o.counts[e] = c;
@@ -1258,14 +1265,16 @@ __device__ __forceinline__ void permute_body(const int32_t* idx, int T, int k, i
       o.dense_tab[s_dexp[e]] = DenseExpert{s_dfirst[e], s_off[e], c | (e << 16), hslot};
       // the tiles in expert order cost dense_cost(c) per feature tile: the
       // XCD boundaries (eighths of the whole) that fall in this expert's
-      // (32 bits: at most 8448 items of cost 13, or 4352 of 17, times 8191
-      // feature tiles; 64-bit divisions here cost the planning 5 us)
+      // (32 bits: an item holds 64.5 rows and more, src and the intermediate
+      // rows are below 2^31 bytes, and k is at most 16, so there are at most
+      // 1.1 million tiles, each of a cost of at most 17; 64-bit divisions here
+      // cost the planning 5 us)
       const uint32_t mine = dense_cost(c, dsh), m = (c + (1 << dsh) - 1) >> dsh, tile = mine / m;
 #pragma unroll
       for (int p = 0; p < 2; ++p) {
         const uint32_t nf = o.dense_nf[p], lo = s_dcost[e] * nf, len = mine * nf;
         const uint32_t eighth = static_cast<uint32_t>(s_stat[15]) * nf / 8;
-        for (uint32_t x = 0; x < 8; ++x)
+        for (uint32_t x = 0; x < 8 && !even; ++x)
           if (eighth * x - lo < len)   // unsigned: lo <= eighth * x < lo + len
             o.dense_start[9 * p + x] = s_dfirst[e] * nf + min((eighth * x - lo) / tile, m * nf);
       }
@@ -1282,11 +1291,12 @@ __device__ __forceinline__ void permute_body(const int32_t* idx, int T, int k, i
     }
   }
   if (tid == 0) o.offsets[E] = s_off[E];
-  if (o.dense_min > 0) {   // unused entries, the tile totals, and the starts if there are no tiles
+  if (o.dense_min > 0) {   // unused entries, the tile totals, and even starts (all 0 without tiles)
     for (int e = tid; e < kMaxExperts; e += nthr)
       if (e >= s_stat[10]) o.dense_tab[e].first = kDenseNone;
     for (int i = tid; i < 18; i += nthr)
-      if (i % 9 == 8 || s_stat[14] == 0) o.dense_start[i] = s_stat[14] * o.dense_nf[i / 9];
+      if (i % 9 == 8 || s_stat[14] == 0 || even)
+        o.dense_start[i] = static_cast<uint32_t>(s_stat[14] * o.dense_nf[i / 9]) * (i % 9) / 8;
   }
 
   if (chunk_base) {   // per-chunk bases for the ranking launch: exclusive scan over chunks

@@ -23,6 +23,8 @@ pytestmark = pytest.mark.gpu
 SPLITS = {
     "edges": [64, 65, 96, 97, 128, 255, 256, 257, 511, 512, 513, 1, 0, 33],
     "one-holds-most": [2305, 65, 64, 2],
+    "few-large": [1300, 700, 520, 1793, 64, 900, 1025, 513],   # tiles counted, not priced
+    "many-large": [577 + 5 * e for e in range(17)],            # one expert more than that takes
     "many-small": [65 + e % 3 for e in range(40)],
 }
 
