@@ -1,14 +1,18 @@
 """The split of the dense-tile launches: experts whose routed rows sit at the
-edges of the streaming / dense threshold, of the 32-row tiles and of the 128- and
-256-row items, and one expert that holds nearly every row, so that the ranges
-of tiles per XCD are as uneven as they get. At hidden 1024 and above the small
-tiles ride in the streaming launches (up to 512 routes per expert on average).
+edges of the streaming / dense threshold, of the 32-row groups and of the 128- and
+256-row items, one expert that holds nearly every row, so that the ranges of tiles
+per XCD are as uneven as they get, and few experts with large items, whose tiles
+the XCDs share by number. At hidden 1024 and above the small tiles ride in the
+streaming launches (up to 512 routes per expert on average).
 
 k = 1 makes every gate 1 and every expert's rows exactly the tokens sent to
 it. Every output row is checked against the oracle in float64; the bound is
 the bf16 bound of the layer outputs, per expert, so that one missing or
 misplaced item (at least a tenth of an expert's rows, each off by about its
-own norm) fails it.
+own norm) fails it. Each pass has activations of its own and starts from outputs
+that are not numbers: the intermediate rows that the pass before left at the same
+places are wrong for it, so a tile dropped in the second pass, where the retained
+experts are hits, fails too.
 """
 import numpy as np
 import pytest
@@ -42,18 +46,21 @@ def test_dense_split(name, H, I):
     expert = rng.permutation(np.repeat(np.arange(E), rows))
     lg = np.zeros((T, E), np.float32)
     lg[np.arange(T), expert] = 4.0
-    xh = W.activations(w, 3, 0, 0, 0)
     raw = W.expert_blocks(w, 3, range(P))
     pool = HN.fill_pool(w, 3, P, raw=raw)
     ctx = HN.make_context(w, pool, max_tokens=T)
     y = torch.empty((T, H), dtype=torch.bfloat16, device="cuda")
     conf = torch.rand(T, device="cuda")
     try:
-        for _ in range(2):   # the second pass runs the retained experts as hits
-            print(f"[split] {name} H={H} I={I}", flush=True)
+        for i in range(2):   # the second pass runs the retained experts as hits
+            print(f"[split] {name} H={H} I={I} pass {i}", flush=True)
+            xh = W.activations(w, 3, 0, 0, i)
+            y.fill_(float("nan"))
             HN.layer_step(ctx, 0, torch.from_numpy(lg).cuda(), conf, HN.to_device(xh), y)
             st = ctx.read_layer_state(0, T)
             assert st["counts"].tolist() == rows
+            if i:   # dense tiles of hits are among them
+                assert np.any((np.asarray(rows) >= 65) & st["resident_before"])
             got = O.decode(HN.from_device(y))
             x = O.decode(xh)
             for e in range(E):
