@@ -46,21 +46,25 @@ def _chain(w, seed, layers, n_iters, n_blocks, out_at=None, out_tokens=None, cap
     layer that shift from layer to layer.
     out_at: set of (layer index, iteration) whose outputs are checked (None: all).
     out_tokens: token rows checked there (None: all).
+    expect_dense: True if the dense tiles run in launches of their own, "ride" if
+    in those of the streaming tiles.
     """
     C = w.capacity if capacity is None else capacity
     _say(f"[chain] {w.name} layers={list(layers)} iters={n_iters} C={C} P={n_blocks} "
          f"copy={copy_mode} report={report}")
     raw = W.expert_blocks(w, seed, range(n_blocks))
     pool = HN.fill_pool(w, seed, n_blocks, raw=raw)
-    prof = oled.profile_mask("ffn_dense_up", "ffn_dense_down") if expect_dense else 0
+    prof = oled.profile_mask("ffn_dense_up", "ffn_dense_down", "ffn_down") if expect_dense else 0
     ctx = HN.make_context(w, pool, capacity=C, n_layers=len(layers), copy_mode=copy_mode,
                           profile_ops=prof)
     lock = LockstepOracle(len(layers), w.n_experts, w.top_k, C)
     ow = OracleWeights(w, seed, n_blocks, len(layers), raw=raw)
     worst = [0.0]
+    down_flops = [0]
 
     def check(i, li, st, y, rep):
         where = f"{w.name} l={layers[li]} i={i}"
+        down_flops[0] += 2 * int(st["counts"].sum()) * w.hidden * w.inter
         o = lock.step(li, W.logits(w, seed, layers[li], 0, i), W.confidence(w, seed, 0, i),
                       st, where)
         check_report(rep, o, w.expert_bytes, where)
@@ -75,10 +79,13 @@ def _chain(w, seed, layers, n_iters, n_blocks, out_at=None, out_tokens=None, cap
 
     try:
         run_schedule_gpu(ctx, w, seed, layers, n_iters, forward, check, report=report)
-        if expect_dense:   # the dense-tile launches ran, with work
+        if expect_dense:   # the dense tiles ran, with work, where they are expected
             ops = ctx.profile_collect()
             for name in ("ffn_dense_up", "ffn_dense_down"):
-                assert any(o[0] == name and o[4] > 0 for o in ops), f"{w.name}: no {name} launch"
+                assert any(o[0] == name and o[4] > 0 for o in ops) == (expect_dense is True), (
+                    f"{w.name}: {name} launches")
+            if expect_dense == "ride":   # every down product, and the dense experts' gate/up
+                assert sum(o[4] for o in ops if o[0] == "ffn_down") > down_flops[0]
     finally:
         ctx.close()
         pool.free()
@@ -238,12 +245,20 @@ DENSE = W.WORKLOADS[1].replace(wid=300, name="dense", dtype="bf16", batch=4, blo
                                n_iters=3, capacity=6)
 
 
+RIDE = DENSE.replace(wid=320, name="dense-ride", hidden=1024)
+
+
+@pytest.mark.parametrize("w", [DENSE, RIDE], ids=lambda w: w.name)
 @pytest.mark.parametrize("copy_mode", ["shader", "sdma"])
-def test_dense_tiles(copy_mode):
-    """Experts with 128+ routed rows run as dense tiles: this block has experts
-    with two 256-row items, one plus a shorter item, exactly 256 rows, a short
-    item only, and fewer than 128 rows (streaming), as hits and as misses."""
-    _chain(DENSE, 1, range(2), 3, 32, copy_mode=copy_mode, expect_dense=True)
+def test_dense_tiles(copy_mode, w):
+    """Experts with 65 and more routed rows run as dense tiles: this block (1024
+    tokens, 256 routes an expert on average) has experts of one, two and three
+    256-row items and of up to five 128-row items, and some below 65 rows
+    (streaming), as hits and as misses. At hidden 1024 with the shader transfer
+    the 128-row items ride in the launches of the streaming tiles; else the
+    256-row items have launches of their own."""
+    ride = w.hidden >= 1024 and copy_mode == "shader"
+    _chain(w, 1, range(2), 3, 32, copy_mode=copy_mode, expect_dense="ride" if ride else True)
 
 
 @pytest.mark.parametrize("H,I", [(256, 512), (768, 1280)])
@@ -258,24 +273,31 @@ def test_dense_tiles_stage_counts(H, I):
            out_tokens=rows, expect_dense=True)
 
 
-def test_dense_tiles_cross_residency_bitwise():
-    """The dense / streaming split depends on the routed rows only, so outputs
-    stay identical across cache states and transfers."""
-    w = DENSE
+@pytest.mark.parametrize("w", [DENSE, RIDE], ids=lambda w: w.name)
+def test_dense_tiles_cross_residency_bitwise(w):
+    """The dense / streaming split depends on the routed rows only, and the cut of
+    an expert's rows into items changes no bit: outputs stay identical across cache
+    states and transfers, also where the shader transfer rides 128-row items in the
+    streaming launches and the copy engine leaves 256-row items to launches of
+    their own. Every pass has activations of its own."""
     pool = HN.fill_pool(w, 1, 32)
     outs = {}
     for C, mode in ((w.n_experts, "shader"), (w.capacity, "shader"), (0, "shader"),
-                    (w.capacity, "sdma")):
+                    (w.n_experts, "sdma"), (w.capacity, "sdma")):
         ctx = HN.make_context(w, pool, capacity=C, n_layers=2, copy_mode=mode)
         got = []
         run_schedule_gpu(ctx, w, 1, range(2), 3, True,
-                         lambda i, li, st, y, rep: got.append(y.copy()))
+                         lambda i, li, st, y, rep: got.append((st["counts"], y.copy())))
         ctx.close()
         outs[(C, mode)] = got
     pool.free()
     base = outs[(w.n_experts, "shader")]
+    for counts, _ in base:
+        assert counts.max() > 256 and np.any((counts > 64) & (counts % 128 != 0))
+    for n, (_, y0) in enumerate(base):
+        assert not any(np.array_equal(y0, y1) for _, y1 in base[:n])
     for key, got in outs.items():
-        for y0, y1 in zip(base, got):
+        for (_, y0), (_, y1) in zip(base, got):
             assert np.array_equal(y0, y1), f"{key}: outputs differ from full residency"
 
 
