@@ -1,9 +1,10 @@
 """oled_route_noalloc (no context, no allocation: its scratch is a file-scope
 device array) against route_block on the same logits: top-k ids, gates,
-histogram, offsets and permutation bit for bit, on two calls in a row with
-the second block smaller, over every routing path (fused launch; one
-wavefront per token with a one-workgroup permutation; one token per lane
-with the chunked permutation); then the non-finite flag."""
+histogram, offsets and permutation bit for bit, on calls in a row with other
+block sizes, over every routing path (one workgroup; the fused launch, also
+several times in a row; one wavefront per token with a one-workgroup or a chunked
+permutation; four tokens per wavefront; a row per lane or per group of lanes);
+then the non-finite flag."""
 import sys
 
 import numpy as np
@@ -59,12 +60,16 @@ def _route_block(ctx, lg_dev, T, conf, s):
     return ctx.read_layer_state(0, T)
 
 
-SEQUENCES = [  # (E, k, [T of each call]): the second call's block is smaller
-    (128, 8, [65535, 3000]),   # one token per lane, chunked permutation
-    (128, 8, [900, 100]),      # one wavefront per token + one-workgroup permutation, then fused
-    (64, 6, [5000, 1000]),     # chunked, then wavefront per token
+SEQUENCES = [  # (E, k, [T of each call]): later calls find what earlier ones left in the scratch
+    (128, 8, [65535, 3000]),   # one row per 4 lanes, chunked permutation, then a wavefront per token
+    (128, 8, [900, 100]),      # wavefront per token + one-workgroup permutation, then one workgroup
+    (64, 6, [5000, 1000]),     # four tokens per wavefront, chunked, then wavefront per token
     (200, 3, [2049, 300]),     # chunked over 200 experts, then fused
-    (8, 2, [37, 5]),           # fused, small
+    (200, 3, [300, 70, 300]),  # fused three times in a row: the counter starts at zero each time
+    (256, 4, [200, 256, 100]),
+    (64, 4, [9000, 257, 33]),  # four tokens per wavefront, then wavefront, then one workgroup
+    (96, 4, [20000, 500]),     # one token per lane, then wavefront per token
+    (8, 2, [37, 5]),           # one workgroup
 ]
 
 
