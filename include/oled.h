@@ -224,10 +224,14 @@ typedef enum {
   OLED_OP_SCORE_RETAIN = 5,
   OLED_OP_H2D = 6,           /* copy-engine copies of one apply_misses, or a
                                 transfer-only launch */
-  OLED_OP_FFN_DENSE_UP = 7,  /* dense-tile gate/up GEMM (bf16 experts with 65+ routed rows) in
-                                a launch of its own; with up to 512 routes per expert on
-                                average it rides in the OLED_OP_FFN_DOWN launches */
-  OLED_OP_FFN_DENSE_DOWN = 8, /* dense-tile down GEMM */
+  OLED_OP_FFN_DENSE_UP = 7,  /* dense-tile gate/up GEMM (bf16 experts with 65+ routed rows,
+                                hidden and inter multiples of 256) in a launch of its own.
+                                With the shader transfer, no cooperative compensation,
+                                hidden >= 1024 and up to 512 routes per expert on average,
+                                the dense tiles of gate/up and down ride in the two
+                                OLED_OP_FFN_DOWN launches instead: those count their bytes
+                                and flops, and neither dense kind is recorded */
+  OLED_OP_FFN_DENSE_DOWN = 8, /* dense-tile down GEMM in a launch of its own (as above) */
   OLED_OP_LAYER_ADAPT = 9,    /* layer-adaptive re-sizing of the capacities */
   OLED_OP_ROUTE_GEMM = 10     /* the gate GEMM of route_block_gate */
 } oled_op_kind;

@@ -721,13 +721,16 @@ __device__ __forceinline__ void dense_tile(const FfnLaunch& a, const WorkItem& i
   }
 }
 
-// Dense tile b of a launch: the tiles are numbered expert by expert; within an expert its items go in groups of at most kDenseGroup,
-// feature tile major inside a group. b (on XCD b % 8) is tile b / 8 of that XCD, whose contiguous range [dense_start[x], dense_start[x+1]) holds an
-// eighth of the tiles' cost. So the tiles running at once on an XCD are all
-// items of one or two experts against a few weight slices: each weight slice
-// and each token block crosses the fabric once, and is then shared through
-// that XCD's L2. The expert of a tile is found by the wavefront at once (4
-// table entries a lane, a ballot), one load deep.
+// Dense tile b of a launch: the tiles are numbered expert by expert; within an
+// expert its items go in groups of at most kDenseGroup, feature tile major
+// inside a group. b (on XCD b % 8) is tile b / 8 of that XCD, whose contiguous
+// range [dense_start[x], dense_start[x+1]) holds an eighth of the tiles' cost
+// (of their number, where large tiles of few experts make up the launch). So
+// the tiles running at once on an XCD are all items of one or two experts
+// against a few weight slices: each weight slice and each token block crosses
+// the fabric once, and is then shared through that XCD's L2. The expert of a
+// tile is found by the wavefront at once (4 table entries a lane, a ballot), one
+// load deep.
 template <bool UP, int RR>
 __device__ __forceinline__ void dense_block(const FfnLaunch& a, int b, u32x4_t (*ring)[RR / 8][64]) {
   constexpr int DF = UP ? 128 : 256;
@@ -807,7 +810,10 @@ struct TileLds {
   floatx4_t buf[(DN && kRing > SLOTS * 64) ? kRing : SLOTS * 64];
 };
 
-// DN: workgroups [nfetch, nfetch + ge) take dense tiles.
+// DN: workgroups [nfetch, nfetch + ge) take dense tiles. Two workgroups share a
+// compute unit, so a wavefront has 256 registers. The 128-row dense tile needs a few
+// more: 4 of them here (20 bytes a lane of scratch) and 2 in k_ffn_mix are read
+// again once a pass of its K loop. The streaming tiles spill nothing.
 template <class TR, bool UP, int KS, bool DN>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DN ? 2 : 1)))
 void k_ffn(FfnLaunch a, int ge) {

@@ -179,8 +179,8 @@ struct FfnLaunch {
 hipError_t launch_router_logits(bool bf16, const void* x, const void* wg, int T, int E, int H,
                                 float* logits, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s);
 
-// K1: top-k + fp64 gates: one wavefront per token, or for large blocks one
-// token per lane.
+// K1: top-k + fp64 gates: one wavefront per token, 16 lanes per token for
+// larger blocks, and for the largest one lane per token or per 32 experts.
 // block_tokens > 0: the T tokens are blocks of that many, and a non-finite
 // logit of token t sets bad_flag[t / block_tokens] (else bad_flag[0]).
 hipError_t launch_route_topk(const float* logits, int T, int E, int k, int32_t* topk_idx,
@@ -232,12 +232,13 @@ hipError_t launch_permute_chunked(const int32_t* topk_idx, int T, int k, int32_t
 // block (routes by T*k, counts by E, offsets by E+1, bad_out by 1).
 // bad_flag: [B] non-finite flags of the top-k launch; chunk_base:
 // [B][permute_chunks(T)][E] scratch.
-// Routing and permutation of B blocks of one chunk (T <= 512), no cache: one launch.
-hipError_t launch_route_blocks(const float* logits, int B, int T, int k, int32_t* topk_idx,
-                               float* gates, const PermuteOut& o, hipStream_t s);
 hipError_t launch_permute_batch(const int32_t* topk_idx, int B, int T, int k,
                                 const int32_t* bad_flag, int32_t* chunk_base, const PermuteOut& o,
                                 hipStream_t s);
+
+// K1+K2 of B such blocks of one chunk (T <= 512) as one launch.
+hipError_t launch_route_blocks(const float* logits, int B, int T, int k, int32_t* topk_idx,
+                               float* gates, const PermuteOut& o, hipStream_t s);
 
 // K1+K2 as one launch for blocks with T*k <= 1024 (route_fused true): one
 // workgroup takes the smallest, else the last workgroup to finish routing

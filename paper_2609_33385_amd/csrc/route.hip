@@ -387,8 +387,8 @@ __global__ __launch_bounds__(256) void k_route_lanes(const float* __restrict__ l
       if (c == 0) reset();
       // wait for DMA(g): issued after it are DMA(g + 1) (8 loads) and, in the
       // first two chunks of every block but the first, the last block's KM
-      // gate loads (issued by every lane, so exactly KM; with one chunk per
-      // block two blocks' loads, of which counting one only waits longer)
+      // gate loads (issued by every lane, so exactly KM; a block has three
+      // chunks and more: 32, 64, 128 and 256 experts take k_route_rows)
       const bool more = g + 1 < total, loads = c <= 1 && bi >= 1;
       if (more) {
         if (loads) route_wait_vmcnt<8 + KM>();
@@ -1781,8 +1781,8 @@ __global__ __launch_bounds__(kPermThreads) void k_route_solo(const float* __rest
 // Small blocks without a cache (T <= kChunkTokens): one workgroup routes, counts
 // and ranks a block, with its routes in LDS, in one launch instead of a clearing,
 // a routing and up to three permutation launches, each bounded by its latency.
-// 16 blocks of 257 tokens x 64 experts (k = 8): 18.7 -> 10.2 us; one of 32: 11.3 ->
-// 4.9 us.
+// 16 blocks of 257 tokens x 64 experts (k = 8): 18.7 -> 9.9 us; one of 32: 11.3 ->
+// 4.7 us.
 template <int LPT, int EPL, int KM>
 __global__ __launch_bounds__(kPermThreads) void k_route_block_batch(
     const float* __restrict__ logits, int T, int k, int32_t* __restrict__ topk_idx,
