@@ -613,11 +613,12 @@ __device__ __forceinline__ void exact_ids(int l, int E, const float* src, int32_
 }
 
 // Whether the tied tokens of a wavefront (a bit each) are ranked one after the
-// other: about 0.2 us a route, against 1, 1.2 and 1.8 us for all of them at once
-// with 4, 8 and 16 experts a lane of 16, and 1.8, 3 and 6 with 16, 32 and 64 of 4.
+// other: about 0.15 us a route and 0.3 us a token, against 1, 1.2 and 1.8 us for all
+// of them at once with 4, 8 and 16 experts a lane of 16, and 1.8, 3 and 6 with 16,
+// 32 and 64 of 4.
 template <int LPT, int EPL>
 __device__ __forceinline__ bool few_tied(uint64_t todo, int k) {
-  return __popcll(todo) * k <= (LPT == 4 ? EPL / 2 : 4 + EPL / 4);
+  return __popcll(todo) * (k + 2) <= (LPT == 4 ? EPL * 5 / 8 : 4 + EPL * 3 / 8);
 }
 
 template <int KM>
@@ -1741,7 +1742,9 @@ __global__ __launch_bounds__(256) void k_route_fused(const float* __restrict__ l
 // one workgroup of 16 wavefronts, the routes handed over in LDS. What bounds
 // these calls is the chain of latencies; the many-workgroup form above adds a
 // device-wide fence, an atomic round trip and a reload of the routes to it.
-// In a layer of 32 tokens x 64 experts (k = 8) the launch took 10.3 us, now 6.2.
+// In a layer of 32 tokens x 64 experts (k = 8), whose GEMMs leave neither its code
+// nor its state in the caches, the launch took 11.1 us, now 9.0; routing and
+// retention in a loop of their own 18.7, now 14.1.
 template <int LPT, int EPL, int KM>
 __global__ __launch_bounds__(kPermThreads) void k_route_solo(const float* __restrict__ logits,
                                                              int T, int k,
