@@ -55,7 +55,8 @@ def test_order_of_ties(kind, T, E, k):
 
 
 def replayed_us(lg, k, n=50):
-    """Time of one routing call among n in a replayed graph, the least of 8 replays."""
+    """Time of one routing call among n in a replayed graph: the least of 20 replays,
+    after 40 that bring the clock up."""
     from paper_2609_33385_amd import oled
     T, E = lg.shape
     dev = torch.from_numpy(lg).cuda()
@@ -72,7 +73,9 @@ def replayed_us(lg, k, n=50):
                 assert oled.oled_route_noalloc(dev, T, E, k, *out, torch.cuda.current_stream()) == 0
         a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
         best = float("inf")
-        for _ in range(8):
+        for _ in range(40):
+            g.replay()
+        for _ in range(20):
             a.record(s)
             g.replay()
             b.record(s)
